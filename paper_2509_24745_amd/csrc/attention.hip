@@ -49,11 +49,30 @@ __device__ __forceinline__ int swap_bits23(int x) {
     return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1);
 }
 
+constexpr int kSubKeys = 64;  // keys per attention sub-block
+
+// Tile layout of a sub-block's K and V^T (in the copy and in LDS alike, so
+// that a tile moves to LDS as one contiguous run).  Both are lines of D
+// elements.  K: line = key.  V^T: row d's KT keys are segment (d / 32) % R of
+// line 32 (d / 32 / R) + d % 32, R = D / KT rows to a line; so lane lc of a
+// wave finds every fragment of both tiles in lines lc, lc + 32, ...  Chunk c
+// (16 bytes) of line l lies at position c ^ (l & 7): an LDS read of one chunk
+// index from 32 lines then meets no bank conflict (85 bytes a clock and CU
+// measured, as from consecutive addresses; 16 without the XOR), as with lines
+// padded by a chunk each, but without the padding's 1/16 to 1/8 of the copies
+// and of the LDS, and with as many copy instructions for every wave.  Against
+// padded lines, 32/8 heads: dense 32K 6.99 -> 6.92 ms, sparse d 128 b 64 12K
+// 536 -> 516 us, d 64 b 64 20K 591 -> 569 us, fp32 8K 1389 -> 1342 us.
+template <typename T, int D>
+__device__ __forceinline__ int line_pos(int line, int elem) {
+    constexpr int V = Vec16<T>::n;
+    return line * D + ((elem / V) ^ (line & 7)) * V;
+}
+
 // ---------------------------------------------------------------------------
 // K, V -> kvb.  grid (Mq, Hkv), 256 threads.  Rows >= N are zero.  Also
 // zeroes the attention work-queue counters.
 // ---------------------------------------------------------------------------
-constexpr int kSubKeys = 64;  // keys per attention sub-block
 
 template <typename T, int D, int B>
 __global__ __launch_bounds__(256) void kv_block_kernel(Shape sh, const T* __restrict__ k,
@@ -81,7 +100,7 @@ __global__ __launch_bounds__(256) void kv_block_kernel(Shape sh, const T* __rest
             xv = *reinterpret_cast<const u32x4*>(vsrc + (int64_t)tok * sh.kv_tok + col);
         }
         // K rows go straight to their sub-block
-        T* kd = dst + (row / KT) * SUB + (row % KT) * D + col;
+        T* kd = dst + (row / KT) * SUB + line_pos<T, D>(row % KT, col);
         *reinterpret_cast<u32x4*>(kd) = xk;
         *reinterpret_cast<u32x4*>(tile + row * LDR + col) = xv;
     }
@@ -98,7 +117,9 @@ __global__ __launch_bounds__(256) void kv_block_kernel(Shape sh, const T* __rest
             const int key = sub * KT + ((p & ~31) | swap_bits23(p & 31));
             put_elem<T>(x, e, tile[key * LDR + d]);
         }
-        *reinterpret_cast<u32x4*>(dst + sub * SUB + KT * D + d * KT + p0) = x;
+        constexpr int R = D / KT;
+        const int line = 32 * (d / 32 / R) + d % 32, elem = (d / 32 % R) * KT + p0;
+        *reinterpret_cast<u32x4*>(dst + sub * SUB + KT * D + line_pos<T, D>(line, elem)) = x;
     }
 }
 
@@ -164,10 +185,8 @@ struct AttnCfg {
     static constexpr int NSUB = B / KT;                // sub-blocks per block
     static constexpr int NT = KT / 32;                 // 32-key tiles per sub-block
     static constexpr int SUB = 2 * KT * D;             // elements of a kvb sub-block
-    static constexpr int KPAD = D + V;                 // padded K row in LDS (elements)
-    static constexpr int VPAD = KT + V;                // padded V^T row in LDS
-    static constexpr int K_ELEMS = KT * KPAD;
-    static constexpr int V_ELEMS = D * VPAD;
+    static constexpr int K_ELEMS = KT * D;             // K tile (swizzled rows)
+    static constexpr int V_ELEMS = D * KT;             // V^T tile
     static constexpr int STAGE = K_ELEMS + V_ELEMS;
     static constexpr int VPT = SUB / V / NTH;          // 16-byte vectors per thread per sub-block
     // Waves per SIMD the LDS of one CU (160 KiB) leaves room for, capped at
@@ -178,69 +197,37 @@ struct AttnCfg {
     static constexpr int MIN_WAVES = WAVES_PER_SIMD_LDS < 1 ? 1 : (WAVES_PER_SIMD_LDS > 2 ? 2 : WAVES_PER_SIMD_LDS);
 };
 
-// Direct global -> LDS copy of one kvb sub-block (K rows, then V^T rows)
-// into the padded LDS layout.  One buffer_load_dwordx4 ... lds moves 64
-// consecutive 16-byte LDS slots (slot = lane); the padded layout has one
-// spare slot per row, which loads a harmless duplicate of the row's first
-// chunk.  The buffer descriptor spans exactly the sub-block (built in SGPRs
-// per copy), so each lane needs one 32-bit offset per instruction, computed
-// once, and the hardware range check keeps every read inside the sub-block.
-// Instructions are dealt to the waves round-robin.
+// Direct global -> LDS copy of one kvb sub-block (a K tile, then a V^T
+// tile, both stored as they lie in LDS).  One buffer_load_dwordx4 ... lds
+// moves 64 consecutive 16-byte slots (slot = lane); a tile's instructions are
+// dealt to the waves round-robin.  The buffer descriptor spans exactly the
+// sub-block (built in SGPRs per copy), so every instruction takes the same
+// lane offset plus a constant, and the hardware range check keeps every read
+// inside the sub-block.
 template <typename T, int D, int KT, int NW>
 struct SubTileDma {
     static constexpr int V = Vec16<T>::n;
-    static constexpr int KSR = D / V + 1;              // slots per padded K row
-    static constexpr int VSR = KT / V + 1;             // slots per padded V^T row
-    static constexpr int K_INS = KT * KSR / 64;        // wave instructions, K part
-    static constexpr int V_INS = D * VSR / 64;         // wave instructions, V^T part
-    static constexpr int KJ = (K_INS + NW - 1) / NW;   // per wave (upper bound)
-    static constexpr int VJ = (V_INS + NW - 1) / NW;
-    static constexpr int SUB_BYTES = 2 * KT * D * (int)sizeof(T);
-    static_assert(KT * KSR % 64 == 0 && D * VSR % 64 == 0, "whole wave instructions");
+    static constexpr int INS = KT * D / V / 64;        // wave instructions per tile
+    static constexpr int J = INS / NW;                 // per wave
+    static constexpr int TILE_BYTES = KT * D * (int)sizeof(T);
+    static_assert(KT * D / V % (64 * NW) == 0, "whole wave instructions, the same for every wave");
 
-    uint32_t koff[KJ], voff[VJ];   // byte offsets inside a sub-block
+    uint32_t off;   // byte offset of this lane's slot of the wave's first instruction
     int w;
 
-    __device__ __forceinline__ SubTileDma(int w_, int lane) : w(w_) {
-#pragma unroll
-        for (int j = 0; j < KJ; ++j) {
-            const int slot = (w + j * NW) * 64 + lane;
-            const int row = slot / KSR, ch = slot % KSR;
-            koff[j] = (uint32_t)((row * D + (ch == KSR - 1 ? 0 : ch * V)) * sizeof(T));
-        }
-#pragma unroll
-        for (int j = 0; j < VJ; ++j) {
-            const int slot = (w + j * NW) * 64 + lane;
-            const int row = slot / VSR, ch = slot % VSR;
-            voff[j] = (uint32_t)((KT * D + row * KT + (ch == VSR - 1 ? 0 : ch * V)) * sizeof(T));
-        }
-    }
-    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const T* sub) {
+    __device__ __forceinline__ SubTileDma(int w_, int lane) : off((w_ * 64 + lane) * 16), w(w_) {}
+    __device__ __forceinline__ void issue(const T* sub, T* lds, int tile) const {
         // raw buffer, 32-bit dword format (CDNA descriptor word 3)
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(sub), 0, SUB_BYTES, 0x00020000);
-    }
-    __device__ __forceinline__ void issue_k(const T* sub, T* k_lds) const {
-        const __amdgpu_buffer_rsrc_t r = rsrc(sub);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(sub), 0, 2 * TILE_BYTES, 0x00020000);
 #pragma unroll
-        for (int j = 0; j < KJ; ++j) {
-            const int ins = w + j * NW;
-            if (KJ * NW == K_INS || ins < K_INS)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    r, (__attribute__((address_space(3))) void*)(k_lds + ins * 64 * V), 16, koff[j],
-                    0, 0, 0);
-        }
+        for (int j = 0; j < J; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                r, (__attribute__((address_space(3))) void*)(lds + (w + j * NW) * 64 * V), 16, off,
+                tile * TILE_BYTES + j * NW * 1024, 0, 0);
     }
-    __device__ __forceinline__ void issue_v(const T* sub, T* v_lds) const {
-        const __amdgpu_buffer_rsrc_t r = rsrc(sub);
-#pragma unroll
-        for (int j = 0; j < VJ; ++j) {
-            const int ins = w + j * NW;
-            if (VJ * NW == V_INS || ins < V_INS)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    r, (__attribute__((address_space(3))) void*)(v_lds + ins * 64 * V), 16, voff[j],
-                    0, 0, 0);
-        }
-    }
+    __device__ __forceinline__ void issue_k(const T* sub, T* k_lds) const { issue(sub, k_lds, 0); }
+    __device__ __forceinline__ void issue_v(const T* sub, T* v_lds) const { issue(sub, v_lds, 1); }
 };
 
 // The two K and two V^T tiles in LDS.  They are four separate variables so
@@ -255,6 +242,39 @@ struct LdsSlots {
     T* v1;
     __device__ __forceinline__ T* k(int p) const { return p ? k1 : k0; }
     __device__ __forceinline__ T* v(int p) const { return p ? v1 : v0; }
+};
+
+// A lane's fragment reads from tile lines (see line_pos): 8 consecutive
+// elements, one chunk of bf16 or two of fp32, of line lc (+ 32, + 64, ...).
+// The XOR touches the low three bits of the chunk number, so four offsets
+// serve every fragment of both tiles; the rest is an immediate.
+template <typename T, int D>
+struct LaneLines {
+    int x[4];   // byte offsets
+    __device__ __forceinline__ LaneLines(int lc, int h) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            x[u] = line_pos<T, D>(lc, sizeof(T) == 2 ? 16 * u + 8 * h
+                                                     : 16 * (u / 2) + 8 * h + 4 * (u % 2)) * (int)sizeof(T);
+    }
+    // Makes the offsets new to the optimizer.  Called in every step: it would
+    // otherwise keep offset + tile address, loop invariants, in registers for
+    // each of the four tiles, where the read's immediate holds the tile's.
+    __device__ __forceinline__ void renew() {
+        asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+    }
+    // elements f + 8 h .. + 7 of the line, f a multiple of 16
+    __device__ __forceinline__ typename FragOf<T>::type frag(const T* tile, int f) const {
+        const char* t = reinterpret_cast<const char*>(tile);
+        if constexpr (sizeof(T) == 2) {
+            return *reinterpret_cast<const typename FragOf<T>::type*>(t + x[f / 16 % 4] + f / 64 * 128);
+        } else {
+            t += f / 32 * 128;
+            const f32x4 a = *reinterpret_cast<const f32x4*>(t + x[f / 16 % 2 * 2]);
+            const f32x4 b = *reinterpret_cast<const f32x4*>(t + x[f / 16 % 2 * 2 + 1]);
+            return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        }
+    }
 };
 
 // Waits for this wave's global -> LDS copies (they count in vmcnt, like any
@@ -349,7 +369,6 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
     typedef AttnCfg<T, D, B> C;
     typedef typename FragOf<T>::type Frag;
     typedef SubTileDma<T, D, C::KT, C::NTH / 64> Dma;
-    static_assert(C::KPAD == Dma::KSR * C::V && C::VPAD == Dma::VSR * C::V, "padded pitches");
     constexpr int NT = C::NT;
     constexpr int DT = D / 32;   // output tiles along d
     constexpr int KS = D / 16;   // k steps of Q K^T
@@ -403,13 +422,20 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
     };
     auto sub_src = [&](int nb, int sub) { return kvbase + (int64_t)nb * (2 * B * D) + sub * C::SUB; };
     auto needs_mask = [&](int nb) { return nb == m || (nb + 1) * B > n_tok; };
+    // this lane's fragments of a K tile (key 32 kt + lc, elements 16 ks + 8 h
+    // .. + 7) and of a V^T tile (row 32 dt + lc, the 8 keys of PV step (kt, e))
+    LaneLines<T, D> lines(lc, h);
+    auto kfrag = [&](const T* kb, int kt, int ks) { return lines.frag(kb + 32 * kt * D, 16 * ks); };
+    auto vfrag = [&](const T* vb, int dt, int kt, int e) {
+        constexpr int R = D / C::KT;
+        return lines.frag(vb + 32 * (dt / R) * D, dt % R * C::KT + 32 * kt + 16 * e);
+    };
     auto qk = [&](f32x16* acc, const T* kt_) {
 #pragma unroll
         for (int kt = 0; kt < NT; ++kt) {
             acc[kt] = zero16();
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                mma(acc[kt], load_frag<T>(kt_ + (32 * kt + lc) * C::KPAD + 16 * ks + 8 * h), qf[ks]);
+            for (int ks = 0; ks < KS; ++ks) mma(acc[kt], kfrag(kt_, kt, ks), qf[ks]);
         }
     };
 
@@ -470,6 +496,7 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
     // scores never wait for the current softmax to free its registers; bf16
     // keeps `sc` only for the step's rescale check).
     auto step = [&](f32x16* sc, f32x16* sn, int st) {
+        lines.renew();
         if constexpr (sizeof(T) == 2) {
             // a masked sub-tile (the diagonal or a ragged end, rare): its
             // probabilities formed again from its masked scores
@@ -549,10 +576,9 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
             const T* kb = slot.k((st + 1) & 1);
             const T* vb = slot.v(st & 1);
             auto frag = [&](int j) -> Frag {
-                if (j < NQ)
-                    return load_frag<T>(kb + (32 * (j % NT) + lc) * C::KPAD + 16 * (j / NT) + 8 * h);
-                const int p = j - NQ, kt = p / (2 * DT), e = (p / DT) % 2, dt = p % DT;
-                return load_frag<T>(vb + (32 * dt + lc) * C::VPAD + 32 * kt + 16 * e + 8 * h);
+                if (j < NQ) return kfrag(kb, j % NT, j / NT);
+                const int p = j - NQ;
+                return vfrag(vb, p % DT, p / (2 * DT), (p / DT) % 2);
             };
             Frag f[NF];
 #pragma unroll
@@ -609,8 +635,7 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
                 for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
                     for (int e = 0; e < 2; ++e)
-                        mma(o[dt], load_frag<T>(vt_ + (32 * dt + lc) * C::VPAD + 32 * kt + 16 * e + 8 * h),
-                            pf[kt][e]);
+                        mma(o[dt], vfrag(vt_, dt, kt, e), pf[kt][e]);
         }
         // --- mask and max of step st+1 (fp32; bf16 masks at the start of the
         // next step and checks its probabilities there)
@@ -634,27 +659,29 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
         // O through LDS: the wave's 32 x D tile is written to the K slots
         // (free once every wave is done with the last step) and read back as
         // 16-byte row chunks, so that each store writes whole 128-byte lines
-        constexpr int OP = D + 8;
-        static_assert(2 * 32 * OP <= C::K_ELEMS, "two waves' O tiles per K slot");
+        static_assert(2 * 32 * D <= C::K_ELEMS, "two waves' O tiles per K slot");
         __syncthreads();
-        T* ot = (w < 2 ? slot.k(0) : slot.k(1)) + (w & 1) * 32 * OP;
+        T* ot = (w < 2 ? slot.k(0) : slot.k(1)) + (w & 1) * 32 * D;
+        // new to the optimizer: no address of the epilogue is an item-loop
+        // invariant kept in a register through the steps
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg) {
-                const int d0 = 32 * dt + 8 * rg + 4 * h;
                 const float v0 = o[dt][4 * rg + 0] * inv, v1 = o[dt][4 * rg + 1] * inv;
                 const float v2 = o[dt][4 * rg + 2] * inv, v3 = o[dt][4 * rg + 3] * inv;
-                *reinterpret_cast<uint2*>(ot + lc * OP + d0) = make_uint2(pack_bf16x2(v0, v1),
-                                                                          pack_bf16x2(v2, v3));
+                *reinterpret_cast<uint2*>(ot + line_pos<T, D>(ln & 31, 32 * dt + 8 * rg) + 4 * (ln >> 5)) =
+                    make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
             }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
-            const int r = 4 * it + (lane >> 4), c = (lane & 15) * 8;
-            const u32x4 val = *reinterpret_cast<const u32x4*>(ot + r * OP + c);
+            const int r = 4 * it + (ln >> 4), c = (ln & 15) * 8;
+            const u32x4 val = *reinterpret_cast<const u32x4*>(ot + line_pos<T, D>(r, c));
             const int tok = m * B + 32 * w + r;
             if (tok < n_tok)
                 *reinterpret_cast<u32x4*>(out + (int64_t)tok * sh.o_tok + (int64_t)i * sh.o_head + c) = val;
