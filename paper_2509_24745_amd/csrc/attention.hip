@@ -2,8 +2,8 @@
 // paragraph) and its dense baseline (every causal block).
 //
 // Work item = (query head i, query block m): b query rows, one wave per 32
-// rows.  The item walks its list of key blocks in sub-blocks of 64 keys; for
-// each sub-block it computes
+// rows.  The item walks its list of key blocks in sub-blocks of 64 keys (32
+// for bf16 with d = 128 and b = 64); for each sub-block it computes
 //   S^T = K Q^T            (32x32x16 bf16 MFMA; K from LDS, Q in registers)
 //   online softmax          (lane-local per query + one half-wave exchange)
 //   O^T += V^T P^T          (P^T straight from the S^T accumulators)
@@ -13,28 +13,22 @@
 // 8(r/4) + 4h + r%4, and the V^T operand is read in that key order.
 //
 // A pre-pass re-blocks K and V once per call into
-//   kvb[h][n][sub] = { K rows of the sub-block (64 x d, row-major),
-//                      V^T of the sub-block (d x 64, keys permuted: bits 2
-//                      and 3 of the offset in each 32-key tile swapped) }
-// so that every sub-block is one contiguous 16*d*8-byte chunk (spread over
+//   kvb[h][n][sub] = { K tile, V^T tile }     (KT keys each, see line_pos)
+// with the keys of V^T permuted (bits 2 and 3 of the offset in each 32-key
+// tile swapped), so that every sub-block is one contiguous chunk (spread over
 // all HBM channels whatever KV head is being read), the 8 keys a lane needs
-// for one PV step are contiguous (one 16-byte LDS read), and rows past N are
-// zero.
+// for one PV step are contiguous, and rows past N are zero.
 //
-// Pipeline (one barrier per 64-key step j; two workgroups share a CU):
-//   - sub-tiles are copied global -> LDS with global_load_lds (no staging
+// Pipeline (one barrier per step j; two workgroups share a CU):
+//   - sub-tiles are copied global -> LDS with buffer loads (no staging
 //     registers); K and V^T have separate double buffers, K one step ahead:
 //     during step j the copies of K(j+2) and V(j+1) run while the wave reads
 //     K(j+1) and V(j);
-//   - the scores of step j+1 (MFMA) are interleaved instruction by
-//     instruction with the softmax of step j (VALU), then PV of step j runs,
-//     as one explicit software pipeline in which every LDS fragment read is
-//     issued two MFMAs ahead of its use;
-//   - the probability sum of step j and the row maxima of step j+1 are
-//     computed inside the PV segments (held there by empty asm operands, so
-//     that the optimizer cannot sink them past the masking branch); a masked
-//     sub-tile (the diagonal block or a ragged end) takes its maxima again
-//     after masking, and the rare rescale branch stays outside the block.
+//   - bf16: the scores of step j+1 (MFMA), then PV of step j, run as one
+//     explicit software pipeline in which every LDS fragment read is issued
+//     kReadLead MFMAs ahead of its use and step j+1's probabilities (VALU)
+//     are formed beside the PV MFMAs; the reference of the online softmax is
+//     checked after the fact, at the start of the next step.
 #include <algorithm>
 #include <mutex>
 #include <vector>
@@ -49,24 +43,33 @@ __device__ __forceinline__ int swap_bits23(int x) {
     return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1);
 }
 
-constexpr int kSubKeys = 64;  // keys per attention sub-block
+// Keys per sub-block (one step of the attention loop).  A workgroup keeps
+// two K and two V^T tiles in LDS.  bf16 at d = 128, b = 64 has two waves to a
+// workgroup, and with 64-key tiles (64 KiB) a CU's LDS holds two of them, one
+// wave per SIMD; 32-key tiles give two (12K tokens, 32/8 heads, sparse: 516
+// -> 434 us).  At d = 64 64-key tiles leave room for two waves per SIMD
+// anyway, and 32-key ones were slower at two, three and four waves (20K, b =
+// 64: 579 against 607, 608, 615 us; b = 128: 534 against 560-570).
+template <typename T, int D, int B>
+constexpr int sub_keys() { return sizeof(T) == 2 && D == 128 && B == 64 ? 32 : 64; }
 
 // Tile layout of a sub-block's K and V^T (in the copy and in LDS alike, so
 // that a tile moves to LDS as one contiguous run).  Both are lines of D
 // elements.  K: line = key.  V^T: row d's KT keys are segment (d / 32) % R of
 // line 32 (d / 32 / R) + d % 32, R = D / KT rows to a line; so lane lc of a
-// wave finds every fragment of both tiles in lines lc, lc + 32, ...  Chunk c
-// (16 bytes) of line l lies at position c ^ (l & 7): an LDS read of one chunk
-// index from 32 lines then meets no bank conflict (85 bytes a clock and CU
-// measured, as from consecutive addresses; 16 without the XOR), as with lines
-// padded by a chunk each, but without the padding's 1/16 to 1/8 of the copies
-// and of the LDS, and with as many copy instructions for every wave.  Against
-// padded lines, 32/8 heads: dense 32K 6.99 -> 6.92 ms, sparse d 128 b 64 12K
-// 536 -> 516 us, d 64 b 64 20K 591 -> 569 us, fp32 8K 1389 -> 1342 us.
+// wave finds every fragment of both tiles in lines lc, lc + 32, ...  Chunks
+// (16 bytes) of a line are XOR-ed in position so that the 16 lanes an LDS
+// read serves at a time, which take one chunk index of 16 consecutive lines,
+// meet all 16 bank groups (256 bytes): lines of 16 or more chunks by
+// line % 16, lines of 8 chunks (two to a bank sweep) by line / 2 % 8.  No bank
+// conflicts, as with lines padded by a chunk each, but without the padding's
+// 1/16 to 1/8 of the copies and of the LDS, and with as many copy
+// instructions for every wave.
 template <typename T, int D>
 __device__ __forceinline__ int line_pos(int line, int elem) {
-    constexpr int V = Vec16<T>::n;
-    return line * D + ((elem / V) ^ (line & 7)) * V;
+    constexpr int V = Vec16<T>::n, P = D / V;
+    static_assert(P >= 8, "lines of at least 8 chunks");
+    return line * D + ((elem / V) ^ (P >= 16 ? line & 15 : line / 2 & 7)) * V;
 }
 
 // ---------------------------------------------------------------------------
@@ -84,7 +87,7 @@ __global__ __launch_bounds__(256) void kv_block_kernel(Shape sh, const T* __rest
         queue[threadIdx.x] = 0;
     constexpr int V = Vec16<T>::n;
     constexpr int LDR = D + V;
-    constexpr int KT = kSubKeys < B ? kSubKeys : B;
+    constexpr int KT = sub_keys<T, D, B>();
     constexpr int SUB = 2 * KT * D;
     __shared__ __attribute__((aligned(16))) T tile[B * LDR];
     const int blk = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
@@ -181,7 +184,7 @@ template <typename T, int D, int B>
 struct AttnCfg {
     static constexpr int V = Vec16<T>::n;
     static constexpr int NTH = 2 * B;                  // B/32 waves
-    static constexpr int KT = kSubKeys < B ? kSubKeys : B;  // keys per sub-block
+    static constexpr int KT = sub_keys<T, D, B>();      // keys per sub-block
     static constexpr int NSUB = B / KT;                // sub-blocks per block
     static constexpr int NT = KT / 32;                 // 32-key tiles per sub-block
     static constexpr int SUB = 2 * KT * D;             // elements of a kvb sub-block
@@ -190,8 +193,8 @@ struct AttnCfg {
     static constexpr int STAGE = K_ELEMS + V_ELEMS;
     static constexpr int VPT = SUB / V / NTH;          // 16-byte vectors per thread per sub-block
     // Waves per SIMD the LDS of one CU (160 KiB) leaves room for, capped at
-    // 2: the kernel's register budget.  d = 128 with b = 64 (two-wave
-    // workgroups), and fp32 at d = 128, are held to one wave per SIMD by LDS.
+    // 2: the kernel's register budget.  fp32 at d = 128, and at b = 64, is
+    // held to one wave per SIMD by LDS.
     static constexpr int LDS_BYTES = 2 * STAGE * (int)sizeof(T) + 16;
     static constexpr int WAVES_PER_SIMD_LDS = (160 * 1024 / LDS_BYTES) * (NTH / 64) / 4;
     static constexpr int MIN_WAVES = WAVES_PER_SIMD_LDS < 1 ? 1 : (WAVES_PER_SIMD_LDS > 2 ? 2 : WAVES_PER_SIMD_LDS);
@@ -246,32 +249,37 @@ struct LdsSlots {
 
 // A lane's fragment reads from tile lines (see line_pos): 8 consecutive
 // elements, one chunk of bf16 or two of fp32, of line lc (+ 32, + 64, ...).
-// The XOR touches the low three bits of the chunk number, so four offsets
-// serve every fragment of both tiles; the rest is an immediate.
+// The XOR touches at most the low four bits of the chunk number, so NX
+// offsets serve every fragment of both tiles; the rest is an immediate.
 template <typename T, int D>
 struct LaneLines {
-    int x[4];   // byte offsets
+    static constexpr int V = Vec16<T>::n;
+    static constexpr int SPAN = D / V >= 16 ? 16 : 8;   // chunks that the XOR mixes
+    static constexpr int NX = SPAN / 2;
+    int x[NX];   // byte offsets: bf16 chunk 2 u + h, fp32 chunk 4 (u / 2) + 2 h + u % 2
     __device__ __forceinline__ LaneLines(int lc, int h) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            x[u] = line_pos<T, D>(lc, sizeof(T) == 2 ? 16 * u + 8 * h
-                                                     : 16 * (u / 2) + 8 * h + 4 * (u % 2)) * (int)sizeof(T);
+        for (int u = 0; u < NX; ++u)
+            x[u] = line_pos<T, D>(lc, (V == 8 ? 2 * u + h : 4 * (u / 2) + 2 * h + u % 2) * V) *
+                   (int)sizeof(T);
     }
     // Makes the offsets new to the optimizer.  Called in every step: it would
     // otherwise keep offset + tile address, loop invariants, in registers for
     // each of the four tiles, where the read's immediate holds the tile's.
     __device__ __forceinline__ void renew() {
-        asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+#pragma unroll
+        for (int u = 0; u < NX; ++u) asm volatile("" : "+v"(x[u]));
     }
     // elements f + 8 h .. + 7 of the line, f a multiple of 16
     __device__ __forceinline__ typename FragOf<T>::type frag(const T* tile, int f) const {
-        const char* t = reinterpret_cast<const char*>(tile);
-        if constexpr (sizeof(T) == 2) {
-            return *reinterpret_cast<const typename FragOf<T>::type*>(t + x[f / 16 % 4] + f / 64 * 128);
+        constexpr int SE = SPAN * V;   // elements the XOR mixes
+        const char* t = reinterpret_cast<const char*>(tile + f / SE * SE);
+        const int u = f % SE / 16;
+        if constexpr (V == 8) {
+            return *reinterpret_cast<const typename FragOf<T>::type*>(t + x[u]);
         } else {
-            t += f / 32 * 128;
-            const f32x4 a = *reinterpret_cast<const f32x4*>(t + x[f / 16 % 2 * 2]);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(t + x[f / 16 % 2 * 2 + 1]);
+            const f32x4 a = *reinterpret_cast<const f32x4*>(t + x[2 * u]);
+            const f32x4 b = *reinterpret_cast<const f32x4*>(t + x[2 * u + 1]);
             return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
         }
     }
@@ -294,7 +302,7 @@ constexpr int kReadLead = 3;
 // 2^7, so its exponent is below log2(2^7 (1 + 2^-8)) < kRescaleSlack.
 constexpr float kLazySum = 128.f;
 
-// Causal / ragged mask of one 64-key sub-tile: keys past `lim` (offset of
+// Causal / ragged mask of one sub-tile: keys past `lim` (offset of
 // the last visible key inside the sub-tile) become -inf.  A key's offset is
 // 32 kt + 8 (r/4) + (r%4) + 4 h; the compile-time part is compared with the
 // per-lane limit lim - 4h.
@@ -323,34 +331,25 @@ __device__ __forceinline__ float tile_max(const f32x16* s) {
 // Sum of the probabilities a lane feeds to the PV product.  bf16: two per
 // v_dot2_f32_bf16 (the sum then matches the rounded P the MFMA consumes).
 template <typename T, int NT>
-__device__ __forceinline__ float prob_sum(const typename FragOf<T>::type (*pf)[2]);
-
-template <>
-__device__ __forceinline__ float prob_sum<bf16, 2>(const bf16x8 (*pf)[2]) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
+__device__ __forceinline__ float prob_sum(const typename FragOf<T>::type (*pf)[2]) {
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
+        for (int e = 0; e < 2; ++e) {
+            if constexpr (sizeof(T) == 2) {
+                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bf16x2 pr = {pf[kt][e][2 * j], pf[kt][e][2 * j + 1]};
-                acc[j] = __builtin_amdgcn_fdot2_f32_bf16(pr, one, acc[j], false);
+                for (int j = 0; j < 4; ++j) {
+                    const bf16x2 pr = {pf[kt][e][2 * j], pf[kt][e][2 * j + 1]};
+                    acc[j] = __builtin_amdgcn_fdot2_f32_bf16(pr, one, acc[j], false);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j & 3] += pf[kt][e][j];
             }
-    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
-}
-
-template <>
-__device__ __forceinline__ float prob_sum<float, 2>(const f32x8 (*pf)[2]) {
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j & 3] += pf[kt][e][j];
+        }
     return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
@@ -372,7 +371,6 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
     constexpr int NT = C::NT;
     constexpr int DT = D / 32;   // output tiles along d
     constexpr int KS = D / 16;   // k steps of Q K^T
-    static_assert(NT == 2, "64-key sub-tiles");
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, lc = lane & 31;
     const int kvh = i / sh.rep;
@@ -491,7 +489,7 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
         form_p(s_cur, neg_ref());
     }
 
-    // One 64-key step.  `sc` holds the scores of step st, `sn` receives those
+    // One step.  `sc` holds the scores of step st, `sn` receives those
     // of step st+1 (two distinct register sets, used alternately, so the next
     // scores never wait for the current softmax to free its registers; bf16
     // keeps `sc` only for the step's rescale check).

@@ -69,7 +69,7 @@ CASES = {
     "fp32_d128_b128_n1000": LLAMA.replace(seq_len=1000, dtype="fp32", num_q_heads=8,
                                           num_kv_heads=2, num_proxy_groups=2),
     # the remaining compiled (dtype, d, b) instantiations; b = 64 with d = 128
-    # is the two-wave workgroup at one wave per SIMD
+    # is the two-wave workgroup with 32-key steps
     "bf16_d128_b64_s4_n3100": LLAMA.replace(seq_len=3100, block_size=64, num_q_heads=16,
                                             num_kv_heads=4, num_proxy_groups=2),
     "bf16_d64_b128_n2600": Workload(name="t", seq_len=2600, num_q_heads=12, num_kv_heads=3,
