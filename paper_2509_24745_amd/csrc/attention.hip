@@ -28,7 +28,10 @@
 //     explicit software pipeline in which every LDS fragment read is issued
 //     kReadLead MFMAs ahead of its use and step j+1's probabilities (VALU)
 //     are formed beside the PV MFMAs; the reference of the online softmax is
-//     checked after the fact, at the start of the next step.
+//     checked after the fact, at the start of the next step;
+//   - fp32: the same MFMA order with three bf16 terms per operand (Split3);
+//     a fragment is split beside the MFMAs of the one before, and a step's
+//     probabilities are formed beside the next step's scores.
 #include <algorithm>
 #include <mutex>
 #include <vector>
@@ -53,24 +56,11 @@ __device__ __forceinline__ int swap_bits23(int x) {
 template <typename T, int D, int B>
 constexpr int sub_keys() { return sizeof(T) == 2 && D == 128 && B == 64 ? 32 : 64; }
 
-// Tile layout of a sub-block's K and V^T (in the copy and in LDS alike, so
-// that a tile moves to LDS as one contiguous run).  Both are lines of D
-// elements.  K: line = key.  V^T: row d's KT keys are segment (d / 32) % R of
-// line 32 (d / 32 / R) + d % 32, R = D / KT rows to a line; so lane lc of a
-// wave finds every fragment of both tiles in lines lc, lc + 32, ...  Chunks
-// (16 bytes) of a line are XOR-ed in position so that the 16 lanes an LDS
-// read serves at a time, which take one chunk index of 16 consecutive lines,
-// meet all 16 bank groups (256 bytes): lines of 16 or more chunks by
-// line % 16, lines of 8 chunks (two to a bank sweep) by line / 2 % 8.  No bank
-// conflicts, as with lines padded by a chunk each, but without the padding's
-// 1/16 to 1/8 of the copies and of the LDS, and with as many copy
-// instructions for every wave.
-template <typename T, int D>
-__device__ __forceinline__ int line_pos(int line, int elem) {
-    constexpr int V = Vec16<T>::n, P = D / V;
-    static_assert(P >= 8, "lines of at least 8 chunks");
-    return line * D + ((elem / V) ^ (P >= 16 ? line & 15 : line / 2 & 7)) * V;
-}
+// Tile layout of a sub-block (in the copy and in LDS alike, so that a tile
+// moves to LDS as one contiguous run): lines of D elements (see line_pos).
+// K: line = key.  V^T: row d's KT keys are segment (d / 32) % R of line
+// 32 (d / 32 / R) + d % 32, R = D / KT rows to a line; so lane lc of a wave
+// finds every fragment of both tiles in lines lc, lc + 32, ...
 
 // ---------------------------------------------------------------------------
 // K, V -> kvb.  grid (Mq, Hkv), 256 threads.  Rows >= N are zero.  Also
@@ -247,51 +237,6 @@ struct LdsSlots {
     __device__ __forceinline__ T* v(int p) const { return p ? v1 : v0; }
 };
 
-// A lane's fragment reads from tile lines (see line_pos): 8 consecutive
-// elements, one chunk of bf16 or two of fp32, of line lc (+ 32, + 64, ...).
-// The XOR touches at most the low four bits of the chunk number, so NX
-// offsets serve every fragment of both tiles; the rest is an immediate.
-template <typename T, int D>
-struct LaneLines {
-    static constexpr int V = Vec16<T>::n;
-    static constexpr int SPAN = D / V >= 16 ? 16 : 8;   // chunks that the XOR mixes
-    static constexpr int NX = SPAN / 2;
-    int x[NX];   // byte offsets: bf16 chunk 2 u + h, fp32 chunk 4 (u / 2) + 2 h + u % 2
-    __device__ __forceinline__ LaneLines(int lc, int h) {
-#pragma unroll
-        for (int u = 0; u < NX; ++u)
-            x[u] = line_pos<T, D>(lc, (V == 8 ? 2 * u + h : 4 * (u / 2) + 2 * h + u % 2) * V) *
-                   (int)sizeof(T);
-    }
-    // Makes the offsets new to the optimizer.  Called in every step: it would
-    // otherwise keep offset + tile address, loop invariants, in registers for
-    // each of the four tiles, where the read's immediate holds the tile's.
-    __device__ __forceinline__ void renew() {
-#pragma unroll
-        for (int u = 0; u < NX; ++u) asm volatile("" : "+v"(x[u]));
-    }
-    // elements f + 8 h .. + 7 of the line, f a multiple of 16
-    __device__ __forceinline__ typename FragOf<T>::type frag(const T* tile, int f) const {
-        constexpr int SE = SPAN * V;   // elements the XOR mixes
-        const char* t = reinterpret_cast<const char*>(tile + f / SE * SE);
-        const int u = f % SE / 16;
-        if constexpr (V == 8) {
-            return *reinterpret_cast<const typename FragOf<T>::type*>(t + x[u]);
-        } else {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(t + x[2 * u]);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(t + x[2 * u + 1]);
-            return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-        }
-    }
-};
-
-// Waits for this wave's global -> LDS copies (they count in vmcnt, like any
-// vector-memory load).  A copy's data is in LDS only once its wave has
-// waited; the barrier after this wait then hands the tiles to the other
-// waves.  (s_waitcnt fields: vmcnt 0, expcnt and lgkmcnt left at their
-// maxima.)
-__device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
 // MFMAs between the LDS read of an operand fragment and the MFMA that uses it
 // (bf16 attention loop).  With the probabilities formed in the PV segments,
 // 3 is 0.3-0.7 % faster than 2 (8K to 128K, sparse and dense; 2 was the
@@ -328,28 +273,22 @@ __device__ __forceinline__ float tile_max(const f32x16* s) {
     return halves_max(fmaxf(fmaxf(c[0], c[1]), fmaxf(c[2], c[3])));
 }
 
-// Sum of the probabilities a lane feeds to the PV product.  bf16: two per
+// Sum of the bf16 probabilities a lane feeds to the PV product, two per
 // v_dot2_f32_bf16 (the sum then matches the rounded P the MFMA consumes).
-template <typename T, int NT>
-__device__ __forceinline__ float prob_sum(const typename FragOf<T>::type (*pf)[2]) {
+template <int NT>
+__device__ __forceinline__ float prob_sum(const bf16x8 (*pf)[2]) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            if constexpr (sizeof(T) == 2) {
-                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
+        for (int e = 0; e < 2; ++e)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bf16x2 pr = {pf[kt][e][2 * j], pf[kt][e][2 * j + 1]};
-                    acc[j] = __builtin_amdgcn_fdot2_f32_bf16(pr, one, acc[j], false);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[j & 3] += pf[kt][e][j];
+            for (int j = 0; j < 4; ++j) {
+                const bf16x2 pr = {pf[kt][e][2 * j], pf[kt][e][2 * j + 1]};
+                acc[j] = __builtin_amdgcn_fdot2_f32_bf16(pr, one, acc[j], false);
             }
-        }
     return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
@@ -396,11 +335,12 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
         return;
     }
 
-    Frag qf[KS];
+    typedef typename OperandOf<T>::type Op;
+    Op qf[KS];
     {
         const T* qrow = q + (int64_t)min(qtok, n_tok - 1) * sh.q_tok + (int64_t)i * sh.q_head;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = load_frag<T>(qrow + 16 * ks + 8 * h);
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = operand(load_frag<T>(qrow + 16 * ks + 8 * h));
     }
 
     const T* kvbase = kvb + (int64_t)kvh * sh.mq * (2 * B * D);
@@ -433,7 +373,7 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
         for (int kt = 0; kt < NT; ++kt) {
             acc[kt] = zero16();
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) mma(acc[kt], kfrag(kt_, kt, ks), qf[ks]);
+            for (int ks = 0; ks < KS; ++ks) mma(acc[kt], operand(kfrag(kt_, kt, ks)), qf[ks]);
         }
     };
 
@@ -525,13 +465,13 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
             // overflow or while a row has no reference) the row max is taken
             // and, where the reference moves, the probabilities formed
             // again: the same decisions and values as taking the max first.
-            float ps = prob_sum<T, NT>(pf);
+            float ps = prob_sum<NT>(pf);
             if (__builtin_amdgcn_ballot_w64(!(ps <= kLazySum) || m_run == kNegInf)) {
                 const float mxs = tile_max<NT>(sc) * sh.scale2;
                 if (__builtin_amdgcn_ballot_w64(mxs > m_run + kRescaleSlack)) {
                     rescale_to(mxs);
                     form_p(sc, neg_ref());
-                    ps = prob_sum<T, NT>(pf);
+                    ps = prob_sum<NT>(pf);
                 }
             }
             l_run += ps;
@@ -619,21 +559,60 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
             for (int r = 8; r < 16; ++r)
                 pf[NT - 1][1][r & 7] = cvt_p<T>(fast_exp2(fmaf(sn[NT - 1][r], sh.scale2, neg_m)));
         } else {
-            qk(sn, slot.k((st + 1) & 1));
+            // The same MFMA order, six bf16 MFMAs per fragment (see Split3).
+            // Segment j issues fragment j's MFMAs beside the split of
+            // fragment j + 1 (44 VALU instructions to 192 MFMA cycles) and
+            // the LDS read of fragment j + 2.  The QK segments also form this
+            // step's probabilities, the PV segments of group g (see above)
+            // split those of group g + 1.  Left to the scheduler in one block,
+            // the splits ran ahead of the MFMAs: 1057 -> 911 us at 8K (32/8
+            // heads, d 128, sparse).
+            constexpr int NQ = NT * KS, NP = NT * 2 * DT, NF = NQ + NP;
+            constexpr int EPQ = 16 * NT / NQ;   // probabilities per QK segment
+            const T* kb = slot.k((st + 1) & 1);
+            const T* vb = slot.v(st & 1);
+            auto frag = [&](int j) -> Frag {
+                if (j < NQ) return kfrag(kb, j % NT, j / NT);
+                const int p = j - NQ;
+                return vfrag(vb, p % DT, p / (2 * DT), (p / DT) % 2);
+            };
 #pragma unroll
-            for (int kt = 0; kt < NT; ++kt)
+            for (int kt = 0; kt < NT; ++kt) sn[kt] = zero16();
+            float ps[4] = {0.f, 0.f, 0.f, 0.f};
+            Op pop[2 * NT];
+            Frag f[NF];
+            f[0] = frag(0);
+            f[1] = frag(1);
+            Op cur = operand(f[0]);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    pf[kt][r >> 3][r & 7] = cvt_p<T>(fast_exp2(fmaf(sc[kt][r], sh.scale2, neg_m)));
-            l_run += prob_sum<T, NT>(pf);
-            const T* vt_ = slot.v(st & 1);
+            for (int j = 0; j < NF; ++j) {
+                Op nxt = cur;
+                if (j + 2 < NF) f[j + 2] = frag(j + 2);
+                if (j + 1 < NF) nxt = operand(f[j + 1]);
+                if (j < NQ) {
+                    mma(sn[j % NT], cur, qf[j / NT]);
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+                    for (int u = 0; u < EPQ; ++u) {
+                        const int e = EPQ * j + u, kt = e / 16, r = e % 16;
+                        const float pr = fast_exp2(fmaf(sc[kt][r], sh.scale2, neg_m));
+                        pf[kt][r >> 3][r & 7] = pr;
+                        ps[r & 3] += pr;
+                    }
+                    if (j == NQ - 1) pop[0] = operand(pf[0][0]);
+                } else {
+                    const int p = j - NQ, g = p / DT;
+                    mma(o[p % DT], cur, pop[g]);
+                    if (g + 1 < 2 * NT) {
 #pragma unroll
-                for (int kt = 0; kt < NT; ++kt)
-#pragma unroll
-                    for (int e = 0; e < 2; ++e)
-                        mma(o[dt], vfrag(vt_, dt, kt, e), pf[kt][e]);
+                        for (int u = 0; u < 4 / DT; ++u)
+                            split3_pair(pop[g + 1], pf[(g + 1) / 2][(g + 1) % 2], p % DT * (4 / DT) + u);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                cur = nxt;
+            }
+            l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
         }
         // --- mask and max of step st+1 (fp32; bf16 masks at the start of the
         // next step and checks its probabilities there)

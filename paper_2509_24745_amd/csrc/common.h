@@ -10,9 +10,9 @@
 // and B through that one slot convention.
 //
 // bf16 operands: one v_mfma_f32_32x32x16_bf16 per 16-wide k step.
-// fp32 operands: the same 8-slot fragments are consumed by eight
-// v_mfma_f32_32x32x2_f32 (slot j of both halves per instruction), so the
-// data layout of every kernel is identical for the two element types.
+// fp32 operands: each is split into three bf16 terms, and six such MFMAs per
+// step form the product (see Split3); the data layout of every kernel is
+// identical for the two element types.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -70,6 +70,59 @@ __device__ __forceinline__ void mma(f32x16& acc, const bf16x8& a, const bf16x8& 
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
 }
 
+// fp32 operands as three bf16 terms: x = hi + mid + lo exactly (hi the top 8
+// significant bits by truncation, so that no finite x overflows; mid and lo
+// by rounding what is left).  A product keeps six of the nine terms: the
+// others are below 2^-24 of it.  Six bf16 MFMAs of 16 k each take 192 cycles
+// where eight fp32 MFMAs of 2 k took 512, and round the accumulator six times
+// instead of eight: against 64 bits the error is 0.7-0.8 of the fp32 MFMAs'
+// (attention outputs 1.2e-6 against 1.5e-6 at 8K; scores 7.4e-8 against
+// 8.4e-8).  Sparse attention 8K, 32/8 heads, d 128: 1340 -> 911 us, dense d 64
+// b 64 5K: 543 -> 347 us.
+struct Split3 {
+    bf16x8 hi, mid, lo;
+};
+// Elements 2 j and 2 j + 1.
+__device__ __forceinline__ void split3_pair(Split3& s, const f32x8& x, int j) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const uint32_t a = __float_as_uint(x[2 * j]), b = __float_as_uint(x[2 * j + 1]);
+    const bf16x2 hi = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(b, a, 0x07060302u));
+    const f32x2 r = {x[2 * j] - __uint_as_float(a & 0xffff0000u),
+                     x[2 * j + 1] - __uint_as_float(b & 0xffff0000u)};
+    const bf16x2 mid = __builtin_convertvector(r, bf16x2);
+    const uint32_t m = __builtin_bit_cast(uint32_t, mid);
+    const f32x2 t = {r[0] - __uint_as_float(m << 16), r[1] - __uint_as_float(m & 0xffff0000u)};
+    const bf16x2 lo = __builtin_convertvector(t, bf16x2);
+    s.hi[2 * j] = hi[0];
+    s.hi[2 * j + 1] = hi[1];
+    s.mid[2 * j] = mid[0];
+    s.mid[2 * j + 1] = mid[1];
+    s.lo[2 * j] = lo[0];
+    s.lo[2 * j + 1] = lo[1];
+}
+__device__ __forceinline__ Split3 split3(const f32x8& x) {
+    Split3 s;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split3_pair(s, x, j);
+    return s;
+}
+// The six products, smallest first.
+__device__ __forceinline__ void mma(f32x16& acc, const Split3& a, const Split3& b) {
+    mma(acc, a.lo, b.hi);
+    mma(acc, a.hi, b.lo);
+    mma(acc, a.mid, b.mid);
+    mma(acc, a.mid, b.hi);
+    mma(acc, a.hi, b.mid);
+    mma(acc, a.hi, b.hi);
+}
+
+// Fragments as the MFMAs take them: bf16 as they are, fp32 split.
+template <typename T> struct OperandOf { typedef bf16x8 type; };
+template <> struct OperandOf<float> { typedef Split3 type; };
+__device__ __forceinline__ bf16x8 operand(const bf16x8& f) { return f; }
+__device__ __forceinline__ Split3 operand(const f32x8& f) { return split3(f); }
+
 __device__ __forceinline__ void mma(f32x16& acc, const f32x8& a, const f32x8& b) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
@@ -79,6 +132,69 @@ template <typename T>
 __device__ __forceinline__ typename FragOf<T>::type load_frag(const T* p) {
     return *reinterpret_cast<const typename FragOf<T>::type*>(p);
 }
+
+// LDS tiles that MFMA fragments are read from: lines of D elements whose
+// 16-byte chunks are XOR-ed in position so that the 16 lanes an LDS read
+// serves at a time, which take one chunk index of 16 consecutive lines, meet
+// all 16 bank groups (256 bytes): lines of 16 or more chunks by line % 16,
+// lines of 8 chunks (two to a bank sweep) by line / 2 % 8.  No bank conflicts,
+// as with lines padded by a chunk each, but no padding to copy or to hold, and
+// a tile is one contiguous run for global -> LDS copies.
+template <int P>
+__device__ __forceinline__ int chunk_xor(int line) {
+    static_assert(P >= 8, "lines of at least 8 chunks");
+    return P >= 16 ? line & 15 : line / 2 & 7;
+}
+template <typename T, int D>
+__device__ __forceinline__ int line_pos(int line, int elem) {
+    constexpr int V = Vec16<T>::n;
+    return line * D + ((elem / V) ^ chunk_xor<D / V>(line)) * V;
+}
+
+// A lane's fragment reads from tile lines (see line_pos): 8 consecutive
+// elements, one chunk of bf16 or two of fp32, of line lc (+ 32, + 64, ...).
+// The XOR touches at most the low four bits of the chunk number, so NX
+// offsets serve every fragment of both tiles; the rest is an immediate.
+template <typename T, int D>
+struct LaneLines {
+    static constexpr int V = Vec16<T>::n;
+    static constexpr int SPAN = D / V >= 16 ? 16 : 8;   // chunks that the XOR mixes
+    static constexpr int NX = SPAN / 2;
+    int x[NX];   // byte offsets: bf16 chunk 2 u + h, fp32 chunk 4 (u / 2) + 2 h + u % 2
+    __device__ __forceinline__ LaneLines(int lc, int h) {
+#pragma unroll
+        for (int u = 0; u < NX; ++u)
+            x[u] = line_pos<T, D>(lc, (V == 8 ? 2 * u + h : 4 * (u / 2) + 2 * h + u % 2) * V) *
+                   (int)sizeof(T);
+    }
+    // Makes the offsets new to the optimizer.  Called in every step: it would
+    // otherwise keep offset + tile address, loop invariants, in registers for
+    // each of the four tiles, where the read's immediate holds the tile's.
+    __device__ __forceinline__ void renew() {
+#pragma unroll
+        for (int u = 0; u < NX; ++u) asm volatile("" : "+v"(x[u]));
+    }
+    // elements f + 8 h .. + 7 of the line, f a multiple of 16
+    __device__ __forceinline__ typename FragOf<T>::type frag(const T* tile, int f) const {
+        constexpr int SE = SPAN * V;   // elements the XOR mixes
+        const char* t = reinterpret_cast<const char*>(tile + f / SE * SE);
+        const int u = f % SE / 16;
+        if constexpr (V == 8) {
+            return *reinterpret_cast<const typename FragOf<T>::type*>(t + x[u]);
+        } else {
+            const f32x4 a = *reinterpret_cast<const f32x4*>(t + x[2 * u]);
+            const f32x4 b = *reinterpret_cast<const f32x4*>(t + x[2 * u + 1]);
+            return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        }
+    }
+};
+
+// Waits for this wave's global -> LDS copies (they count in vmcnt, like any
+// vector-memory load).  A copy's data is in LDS only once its wave has
+// waited; the barrier after this wait then hands the tiles to the other
+// waves.  (s_waitcnt fields: vmcnt 0, expcnt and lgkmcnt left at their
+// maxima.)
+__device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 __device__ __forceinline__ f32x16 zero16() {
     f32x16 z;
