@@ -78,7 +78,7 @@ __device__ __forceinline__ void mma(f32x16& acc, const bf16x8& a, const bf16x8& 
 // instead of eight: against 64 bits the error is 0.7-0.8 of the fp32 MFMAs'
 // (attention outputs 1.2e-6 against 1.5e-6 at 8K; scores 7.4e-8 against
 // 8.4e-8).  Sparse attention 8K, 32/8 heads, d 128: 1340 -> 911 us, dense d 64
-// b 64 5K: 543 -> 347 us.
+// b 64 5K: 543 -> 347 us, estimate 8K: 128 -> 96 us.
 struct Split3 {
     bf16x8 hi, mid, lo;
 };
@@ -122,11 +122,6 @@ template <typename T> struct OperandOf { typedef bf16x8 type; };
 template <> struct OperandOf<float> { typedef Split3 type; };
 __device__ __forceinline__ bf16x8 operand(const bf16x8& f) { return f; }
 __device__ __forceinline__ Split3 operand(const f32x8& f) { return split3(f); }
-
-__device__ __forceinline__ void mma(f32x16& acc, const f32x8& a, const f32x8& b) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
-}
 
 template <typename T>
 __device__ __forceinline__ typename FragOf<T>::type load_frag(const T* p) {

@@ -11,11 +11,19 @@
 // owns one 16-byte slice of one pooled row.
 //
 // All score tiles are computed transposed, S^T = K Q^T, on the 32x32 MFMA
-// tile: lane l then owns one query (column l % 32) and 16 keys of it, so row
-// statistics (max, sum) are lane-local plus one exchange between the two
-// wave halves.  Key tiles of 32 rows are staged through LDS (double
-// buffered) and shared by the 4 waves of a workgroup; query fragments stay in
-// registers for the whole key loop.
+// tile: lane l then owns one query (column l % 32) and 16 keys of it per
+// tile, so row statistics (max, sum) are lane-local plus one exchange between
+// the two wave halves.  Steps of 64 keys are copied global -> LDS without
+// staging registers (double buffered, one barrier a step) and shared by the 4
+// waves of a workgroup; query fragments stay in registers for the whole key
+// loop.
+// Bound: the VALU (per score a maximum, an FMA, an exp2 and an addition) beside
+// the MFMAs, at the chip's power limit (VALU busy in 70 % and MFMA in 41 % of
+// cycles at 1.8 GHz).  Against 32-key tiles staged through registers, with a
+// running maximum per tile: estimate call 128K 1010 -> 942 us, 50K stride 2
+// 953 -> 882 us, d 64 b 64 32K 114 -> 93 us, b 64 16K 61 -> 55 us.  Measured and
+// not taken: the exponentials of the step before interleaved with the MFMAs
+// (as fast), workgroups of 8 waves that halve the copies (+-2 %).
 //
 // Proxy scores (a2 + a3):
 //   est_rowmax: one pass over the strided causal keys per strided query row,
@@ -58,54 +66,107 @@
 
 namespace pa {
 
-// Stages a tile of 32 consecutive key rows [row0, row0 + 32) x D (row-major,
-// `ld` elements between rows, rows >= nrows read as zero) through registers
-// into an LDS tile with rows padded by 16 bytes.
-template <typename T, int D, int NTH>
-struct KeyTile {
-    static constexpr int V = Vec16<T>::n;
-    static constexpr int LDT = D + V;
-    static constexpr int VECS = 32 * D / V;
-    static constexpr int PER = (VECS + NTH - 1) / NTH;
-    u32x4 reg[PER];
+// Keys of one step of the score kernels (one barrier each).
+constexpr int kStepKeys = 64;
 
-    __device__ __forceinline__ void load(const T* base, int64_t ld, int row0, int nrows, int tid) {
+// Direct global -> LDS copies of the steps' key tiles: keys [64 st, 64 st +
+// 64) of `base` (`ld` elements between rows), line = key - 64 st (see
+// line_pos).  One instruction moves 64 consecutive 16-byte slots of the tile;
+// each of the 4 waves issues INS of them, and a lane keeps one address per
+// instruction, moved on by one step per copy.  Rows past the last are read
+// as the last row (their scores are masked).
+template <typename T, int D>
+struct StepCopy {
+    static constexpr int V = Vec16<T>::n;
+    static constexpr int P = D / V;                      // chunks per line
+    static constexpr int INS = kStepKeys * P / 64 / 4;   // instructions per wave
+    static constexpr int ELEMS = kStepKeys * D;
+    const T* src[INS];
+    const T* base;
+    int64_t ld, step_elems;
+    int nrows, w, lane;
+
+    __device__ __forceinline__ StepCopy(const T* b, int64_t ld_, int nrows_, int first_step, int w_,
+                                        int lane_)
+        : base(b), ld(ld_), step_elems(ld_ * kStepKeys), nrows(nrows_), w(w_), lane(lane_) {
 #pragma unroll
-        for (int c = 0; c < PER; ++c) {
-            const int vi = tid + c * NTH;
-            if (PER * NTH == VECS || vi < VECS) {
-                const int row = vi / (D / V), col = (vi % (D / V)) * V;
-                if (row0 + row < nrows)
-                    reg[c] = *reinterpret_cast<const u32x4*>(base + (int64_t)(row0 + row) * ld + col);
-                else
-                    reg[c] = zero_u32x4();
-            }
-        }
+        for (int j = 0; j < INS; ++j)
+            src[j] = base + (int64_t)(first_step * kStepKeys + line(j)) * ld + chunk(j) * V;
     }
-    __device__ __forceinline__ void store(T* lds, int tid) const {
+    __device__ __forceinline__ int line(int j) const { return ((w * INS + j) * 64 + lane) / P; }
+    __device__ __forceinline__ int chunk(int j) const { return lane % P ^ chunk_xor<P>(line(j)); }
+    // Copies step st; called for consecutive steps from first_step on.
+    __device__ __forceinline__ void issue(int st, T* lds) {
+        const bool whole = (st + 1) * kStepKeys <= nrows;
 #pragma unroll
-        for (int c = 0; c < PER; ++c) {
-            const int vi = tid + c * NTH;
-            if (PER * NTH == VECS || vi < VECS) {
-                const int row = vi / (D / V), col = (vi % (D / V)) * V;
-                *reinterpret_cast<u32x4*>(lds + row * LDT + col) = reg[c];
+        for (int j = 0; j < INS; ++j) {
+            const T* p = src[j];
+            if (!whole) {
+                const int row = min(st * kStepKeys + line(j), nrows - 1);
+                p = base + (int64_t)row * ld + chunk(j) * V;
             }
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)p,
+                (__attribute__((address_space(3))) void*)(lds + (w * INS + j) * 64 * V), 16, 0, 0);
+            src[j] += step_elems;
         }
     }
 };
 
-// S^T tile (32 keys x 32 queries) of one wave: keys from an LDS tile,
-// queries from register fragments.  Lane (lc, h) receives the 16 keys
-// c_row(r, h) of query lc.
+// Scores of one step, transposed (64 keys x 32 queries of one wave): lane
+// (lc, h) receives the keys 32 kt + c_row(r, h) of query lc.
 template <typename T, int D>
-__device__ __forceinline__ f32x16 st_tile(const T* lds_tile, const typename FragOf<T>::type* qf,
-                                          int lc, int h) {
-    constexpr int LDT = D + Vec16<T>::n;
-    f32x16 acc = zero16();
+__device__ __forceinline__ void step_scores(f32x16 (&acc)[2], const T* tile,
+                                            const LaneLines<T, D>& lines,
+                                            const typename OperandOf<T>::type* qf) {
+    acc[0] = zero16();
+    acc[1] = zero16();
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks)
-        mma(acc, load_frag<T>(lds_tile + lc * LDT + 16 * ks + 8 * h), qf[ks]);
-    return acc;
+    for (int ks = 0; ks < D / 16; ++ks) {
+        mma(acc[0], operand(lines.frag(tile, 16 * ks)), qf[ks]);
+        mma(acc[1], operand(lines.frag(tile + 32 * D, 16 * ks)), qf[ks]);
+    }
+}
+
+// Keys past offset `lim` of the step (the query's last visible key) become -inf.
+__device__ __forceinline__ void step_mask(f32x16 (&acc)[2], int lim, int h) {
+    const int lim_h = lim - 4 * h;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            acc[kt][r] = 32 * kt + 8 * (r >> 2) + (r & 3) <= lim_h ? acc[kt][r] : kNegInf;
+}
+
+__device__ __forceinline__ float max8(const f32x16& a, int r0) {
+    return fmaxf(fmaxf(fmaxf(a[r0], a[r0 + 1]), fmaxf(a[r0 + 2], a[r0 + 3])),
+                 fmaxf(fmaxf(a[r0 + 4], a[r0 + 5]), fmaxf(a[r0 + 6], a[r0 + 7])));
+}
+
+// Sum of exp2(scale2 s + neg) over a step's scores: eight chains of four, then
+// pairwise (as many additions as one chain, with shorter rounding paths).
+__device__ __forceinline__ float step_sum(const f32x16 (&acc)[2], float scale2, float neg) {
+    float c[8];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+        const float x = fast_exp2(fmaf(acc[e / 16][e % 16], scale2, neg));
+        c[e % 8] = e < 8 ? x : c[e % 8] + x;
+    }
+    return ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+}
+
+// Slack (log2 units) by which a step's maximum may exceed the reference of a
+// running sum of exp2 before the sum is rescaled: the usual step needs no
+// rescaling, and the largest terms' exponents stay below 1, where their
+// rounding is small (a slack of 8 raised the scores' error against 64 bits by
+// 8 % and was no faster; none at all costs 0.5-1.5 %).
+constexpr float kSumSlack = 1.f;
+
+// max over both wave halves of a in lanes 0..31 and of b in lanes 32..63
+__device__ __forceinline__ float halves_max2(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // ---------------------------------------------------------------------------
@@ -189,84 +250,103 @@ __device__ __forceinline__ void est_rowmax_body(const Shape& sh, const T* __rest
                                                 float* __restrict__ rbm,
                                                 float2* __restrict__ rowpart, int R0, int c, int g,
                                                 int64_t tri_base, int64_t tri_count) {
-    typedef typename FragOf<T>::type Frag;
+    typedef typename OperandOf<T>::type Op;
+    typedef StepCopy<T, D> Copy;
     constexpr int KS = D / 16;
-    __shared__ __attribute__((aligned(16))) T tiles[2][32 * KeyTile<T, D, 256>::LDT];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, lc = lane & 31;
+    __shared__ __attribute__((aligned(16))) T tile0[Copy::ELEMS];
+    __shared__ __attribute__((aligned(16))) T tile1[Copy::ELEMS];
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, lc = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int np = sh.np;
-    const int kt_begin = c * sh.est_kc;
-    const T* qbase = qg + (int64_t)g * np * D;
-    const T* kbase = kg + (int64_t)g * np * D;
-    const int row = R0 + 32 * w + lc;
-    const bool wave_on = R0 + 32 * w < np;
-    const int diag_tile = (R0 + 32 * w) / 32;   // the wave's rows all lie in this key tile
-    const int wave_last_tile = wave_on ? diag_tile : -1;
+    const int kt_begin = c * sh.est_kc;                    // a multiple of 4: 128 keys
     const int last_row_tile = min(R0 + 127, np - 1) / 32;
     if (kt_begin > last_row_tile) return;   // the whole workgroup: no barrier skipped
-    const int last_tile = min(last_row_tile, kt_begin + sh.est_kc - 1);
+    const int s0 = kt_begin / 2, s1 = min(last_row_tile, kt_begin + sh.est_kc - 1) / 2;
+    const int row0 = R0 + 32 * w, row = row0 + lc;
+    // the wave's steps end with its diagonal
+    const int ws1 = row0 < np ? min(s1, (row0 + 31) / kStepKeys) : s0 - 1;
     const float scale2 = sh.scale2;
 
-    Frag qf[KS];
+    const T* kbase = kg + (int64_t)g * np * D;
+    Copy copy(kbase, D, np, s0, w, lane);
+    copy.issue(s0, tile0);
+    Op qf[KS];
     {
-        const T* qrow = qbase + (int64_t)min(row, np - 1) * D;
+        const T* qrow = qg + ((int64_t)g * np + min(row, np - 1)) * D;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = load_frag<T>(qrow + 16 * ks + 8 * h);
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = operand(load_frag<T>(qrow + 16 * ks + 8 * h));
     }
-    float* rbm_g = rbm + ((int64_t)g * tri_count - tri_base) * BP;
+    LaneLines<T, D> lines(lc, h);
 
-    // running max m (scaled, log2 units) and sum l of exp2(c' s - m)
-    float m = kNegInf, l = 0.f, bm = kNegInf;
-    KeyTile<T, D, 256> kt_ld;
-    kt_ld.load(kbase, D, kt_begin * 32, np, tid);
-    kt_ld.store(tiles[kt_begin & 1], tid);
-    __syncthreads();
-    for (int kt = kt_begin; kt <= last_tile; ++kt) {
-        if (kt < last_tile) kt_ld.load(kbase, D, (kt + 1) * 32, np, tid);
-        if (kt <= wave_last_tile) {
-            f32x16 acc = st_tile<T, D>(tiles[kt & 1], qf, lc, h);
-            if (kt == diag_tile) {
+    // Block maxima of a step: NV values a lane, value v (of lane half h) of
+    // block first + 2 v + h for b' <= 32 (the halves take two blocks), of the
+    // step's one block for b' >= 64 (half 0 stores it).  They are stored
+    // after the next step's barrier, so that a wait for copies never waits
+    // for a store just issued.
+    constexpr int NV = BP == 16 ? 2 : 1, BPS = BP <= 32 ? kStepKeys / BP : 1;
+    const int mr = row / BP;
+    float* rrow = rbm + ((int64_t)g * tri_count - tri_base + tri_index(mr, 0)) * BP + row % BP;
+    const int nmax = row >= np || (BP >= 64 && h) ? -1 : mr;   // last block to store
+    float pend[NV];
+    int pend_n = -1;   // first block of the pending values
+    auto flush = [&]() {
+        if (pend_n < 0) return;
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[r] = (kt * 32 + c_row(r, h) <= row) ? acc[r] : kNegInf;
-            }
-            // raw maxima (the scale is positive, so it commutes with max)
-            float c4[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                c4[j] = fmaxf(fmaxf(acc[4 * j], acc[4 * j + 1]), fmaxf(acc[4 * j + 2], acc[4 * j + 3]));
-            const float tm = fmaxf(fmaxf(c4[0], c4[1]), fmaxf(c4[2], c4[3])) * scale2;
-            // a lane half can have all of its keys masked so far (mn = -inf):
+        for (int v = 0; v < NV; ++v) {
+            const int n = BP <= 32 ? pend_n + 2 * v + h : pend_n;
+            if (n <= nmax) rrow[(int64_t)n * BP] = pend[v];
+        }
+        pend_n = -1;
+    };
+
+    // reference m (scaled, log2 units) and sum l of the running sum
+    float m = kNegInf, neg = 0.f, l = 0.f, bm = kNegInf;
+    auto step = [&](int st, T* cur, T* next) {
+        lines.renew();
+        wait_copies();      // tile st has landed ...
+        __syncthreads();    // ... for every wave, and all are done with st - 1
+        flush();
+        if (st < s1) copy.issue(st + 1, next);
+        if (st > ws1) return;
+        f32x16 acc[2];
+        step_scores<T, D>(acc, cur, lines, qf);
+        const int k0 = st * kStepKeys;
+        if (k0 + kStepKeys - 1 > row0) step_mask(acc, row - k0, h);
+        // raw maxima (the scale is positive, so it commutes with max)
+        const float a0 = max8(acc[0], 0), a1 = max8(acc[0], 8);
+        const float b0 = max8(acc[1], 0), b1 = max8(acc[1], 8);
+        const float ta = fmaxf(a0, a1), tb = fmaxf(b0, b1), tm = fmaxf(ta, tb) * scale2;
+        if (__builtin_amdgcn_ballot_w64(tm > m + kSumSlack)) {
+            // a lane half can have all of its keys masked so far (m = -inf):
             // it then adds exp2(-inf) = 0 and keeps l = 0
             const float mn = fmaxf(m, tm);
-            const float neg = (mn == kNegInf) ? 0.f : -mn;
-            const float alpha = (m == kNegInf) ? 0.f : fast_exp2(m - mn);
-            float sp[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sp[r & 3] += fast_exp2(fmaf(acc[r], scale2, neg));
-            l = fmaf(l, alpha, (sp[0] + sp[1]) + (sp[2] + sp[3]));
+            l *= m == kNegInf ? 0.f : fast_exp2(m - mn);
             m = mn;
-            if constexpr (BP == 16) {
-                // one 32-key tile holds two key blocks: slots r < 8 and r >= 8
-                const float s0 = halves_max(fmaxf(c4[0], c4[1]) * scale2);
-                const float s1 = halves_max(fmaxf(c4[2], c4[3]) * scale2);
-                if (h == 0 && row < np) {
-                    const int mr = row / 16, j = row % 16, n0 = 2 * kt;
-                    if (n0 <= mr) rbm_g[tri_index(mr, n0) * 16 + j] = s0;
-                    if (n0 + 1 <= mr) rbm_g[tri_index(mr, n0 + 1) * 16 + j] = s1;
-                }
-            } else {
-                constexpr int TPB = BP / 32;  // key tiles per block
-                const float sm = halves_max(tm);
-                bm = (kt % TPB == 0) ? sm : fmaxf(bm, sm);
-                if ((kt % TPB == TPB - 1 || kt == wave_last_tile) && h == 0 && row < np) {
-                    const int mr = row / BP, j = row % BP, n = kt / TPB;
-                    rbm_g[tri_index(mr, n) * BP + j] = bm;
-                }
+            neg = m == kNegInf ? 0.f : -m;
+        }
+        l += step_sum(acc, scale2, neg);
+        if constexpr (BP == 16) {   // slots r < 8 and r >= 8 of a tile are two blocks
+            pend[0] = halves_max2(a0, a1) * scale2;
+            pend[1] = halves_max2(b0, b1) * scale2;
+            pend_n = 4 * st;
+        } else if constexpr (BP == 32) {
+            pend[0] = halves_max2(ta, tb) * scale2;
+            pend_n = 2 * st;
+        } else {
+            const float sm = halves_max(tm);
+            constexpr int SPB = BP / kStepKeys;   // steps per block
+            bm = SPB == 1 || st % SPB == 0 ? sm : fmaxf(bm, sm);
+            if (SPB == 1 || st % SPB == SPB - 1 || st == ws1) {
+                pend[0] = bm;
+                pend_n = st / SPB;
             }
         }
-        if (kt < last_tile) kt_ld.store(tiles[(kt + 1) & 1], tid);
-        __syncthreads();
+    };
+    for (int st = s0; st <= s1; st += 2) {
+        step(st, tile0, tile1);
+        if (st < s1) step(st + 1, tile1, tile0);
     }
+    flush();
     const float mo = swap_halves(m), lo = swap_halves(l);
     const float mm = fmaxf(m, mo);
     if (h == 0 && row < np) {
@@ -367,74 +447,78 @@ template <typename T, int D, int B>
 __device__ __forceinline__ void mass_block_body(const Shape& sh, const T* __restrict__ q,
                                                 const T* __restrict__ k,
                                                 float2* __restrict__ part, int c, int i) {
-    typedef typename FragOf<T>::type Frag;
-    constexpr int NTH = 256;
+    typedef typename OperandOf<T>::type Op;
+    typedef StepCopy<T, D> Copy;
     static_assert(B <= 128, "at most 4 waves of 32 last-block rows");
-    __shared__ __attribute__((aligned(16))) T tiles[2][32 * KeyTile<T, D, NTH>::LDT];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, lc = lane & 31;
+    constexpr int SPB = B / kStepKeys;   // steps per block
+    __shared__ __attribute__((aligned(16))) T tile0[Copy::ELEMS];
+    __shared__ __attribute__((aligned(16))) T tile1[Copy::ELEMS];
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, lc = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kvh = i / sh.rep;
     const int n = sh.n;
     const int nrows = min(B, n), t0 = n - nrows;
     const int rl = 32 * w + lc, t = t0 + rl;
     const bool wave_on = 32 * w < nrows;
     const int wave_first_t = t0 + 32 * w;
-    const int wave_last_t = t0 + min(32 * w + 31, nrows - 1);
     const int key0 = c * sh.mass_chunk, key1 = min(key0 + sh.mass_chunk, n);
-    const int kt0 = key0 / 32, kt1 = (key1 - 1) / 32;
-    const T* kbase = k + (int64_t)kvh * sh.kv_head;
+    const int s0 = key0 / kStepKeys, s1 = (key1 - 1) / kStepKeys;
 
-    Frag qf[D / 16];
+    Copy copy(k + (int64_t)kvh * sh.kv_head, sh.kv_tok, n, s0, w, lane);
+    copy.issue(s0, tile0);
+    Op qf[D / 16];
     {
         const T* qrow = q + (int64_t)min(t, n - 1) * sh.q_tok + (int64_t)i * sh.q_head;
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = load_frag<T>(qrow + 16 * ks + 8 * h);
+        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = operand(load_frag<T>(qrow + 16 * ks + 8 * h));
     }
-    // this lane's running (max, sum of exp2) over its keys of the current block
-    float bm = kNegInf, bs = 0.f;
-    KeyTile<T, D, NTH> ld;
-    ld.load(kbase, sh.kv_tok, kt0 * 32, n, tid);
-    ld.store(tiles[0], tid);
-    __syncthreads();
-    for (int kt = kt0; kt <= kt1; ++kt) {
-        const int buf = (kt - kt0) & 1;
-        if (kt < kt1) ld.load(kbase, sh.kv_tok, (kt + 1) * 32, n, tid);
-        if (wave_on && kt * 32 <= wave_last_t) {
-            f32x16 acc = st_tile<T, D>(tiles[buf], qf, lc, h);
-            // only tiles reaching past the wave's first row need the causal mask
-            if (kt * 32 + 31 > wave_first_t) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[r] = (kt * 32 + c_row(r, h) <= t) ? acc[r] : kNegInf;
-            }
-            float c4[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                c4[j] = fmaxf(fmaxf(acc[4 * j], acc[4 * j + 1]), fmaxf(acc[4 * j + 2], acc[4 * j + 3]));
-            const float tm = fmaxf(fmaxf(c4[0], c4[1]), fmaxf(c4[2], c4[3])) * sh.scale2;
-            const float mn = fmaxf(bm, tm);
-            if (mn != kNegInf) {
-                const float neg = -mn;
-                float sp[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sp[r & 3] += fast_exp2(fmaf(acc[r], sh.scale2, neg));
-                bs = fmaf(bs, bm == kNegInf ? 0.f : fast_exp2(bm - mn), (sp[0] + sp[1]) + (sp[2] + sp[3]));
-                bm = mn;
-            }
+    LaneLines<T, D> lines(lc, h);
+    float2* prow = part + ((int64_t)i * B + rl) * sh.mq;
+    float2 pend = make_float2(0.f, 0.f);
+    int pend_n = -1;   // block of the pending pair (stored after the next barrier)
+    auto flush = [&]() {
+        if (pend_n < 0) return;
+        if (wave_on && h == 0 && rl < nrows) prow[pend_n] = pend;
+        pend_n = -1;
+    };
+    // the block's reference m (both halves of a row share it) and this lane's
+    // sum
+    float m = kNegInf, neg = 0.f, l = 0.f;
+    auto step = [&](int st, T* cur, T* next) {
+        lines.renew();
+        wait_copies();      // tile st has landed ...
+        __syncthreads();    // ... for every wave, and all are done with st - 1
+        flush();
+        if (st < s1) copy.issue(st + 1, next);
+        if (!wave_on) return;
+        f32x16 acc[2];
+        step_scores<T, D>(acc, cur, lines, qf);
+        const int k0 = st * kStepKeys;
+        // only steps reaching past the wave's first row need the causal mask
+        if (k0 + kStepKeys - 1 > wave_first_t) step_mask(acc, t - k0, h);
+        const float tm = halves_max(fmaxf(fmaxf(max8(acc[0], 0), max8(acc[0], 8)),
+                                          fmaxf(max8(acc[1], 0), max8(acc[1], 8)))) * sh.scale2;
+        if (SPB == 1 || st % SPB == 0) {   // a new block
+            m = tm;
+            neg = m == kNegInf ? 0.f : -m;
+            l = 0.f;
+        } else if (__builtin_amdgcn_ballot_w64(tm > m + kSumSlack)) {
+            const float mn = fmaxf(m, tm);
+            l *= m == kNegInf ? 0.f : fast_exp2(m - mn);
+            m = mn;
+            neg = m == kNegInf ? 0.f : -m;
         }
-        if (((kt + 1) * 32) % B == 0 || kt == kt1) {
-            // block done: combine the two lane halves (one row) and store
-            const float mo = swap_halves(bm), so = swap_halves(bs);
-            const float mm = fmaxf(bm, mo);
-            const float ss = (bm == kNegInf ? 0.f : bs * fast_exp2(bm - mm)) +
-                             (mo == kNegInf ? 0.f : so * fast_exp2(mo - mm));
-            if (wave_on && h == 0 && rl < nrows)
-                part[((int64_t)i * B + rl) * sh.mq + (kt * 32) / B] = make_float2(mm, ss);
-            bm = kNegInf;
-            bs = 0.f;
+        l += step_sum(acc, sh.scale2, neg);
+        if (SPB == 1 || st % SPB == SPB - 1 || st == s1) {
+            pend = make_float2(m, halves_sum(l));
+            pend_n = st / SPB;
         }
-        if (kt < kt1) ld.store(tiles[buf ^ 1], tid);
-        __syncthreads();
+    };
+    for (int st = s0; st <= s1; st += 2) {
+        step(st, tile0, tile1);
+        if (st < s1) step(st + 1, tile1, tile0);
     }
+    flush();
 }
 
 // Row normalisers: one wave per last-block row, 4 rows per 256-thread
