@@ -2,8 +2,8 @@
 // paragraph) and its dense baseline (every causal block).
 //
 // Work item = (query head i, query block m): b query rows, one wave per 32
-// rows.  The item walks its list of key blocks in sub-blocks of 64 keys (32
-// for bf16 with d = 128 and b = 64); for each sub-block it computes
+// rows.  The item walks its list of key blocks in sub-blocks of 64 or 32
+// keys (see sub_keys); for each sub-block it computes
 //   S^T = K Q^T            (32x32x16 bf16 MFMA; K from LDS, Q in registers)
 //   online softmax          (lane-local per query + one half-wave exchange)
 //   O^T += V^T P^T          (P^T straight from the S^T accumulators)
@@ -47,14 +47,19 @@ __device__ __forceinline__ int swap_bits23(int x) {
 }
 
 // Keys per sub-block (one step of the attention loop).  A workgroup keeps
-// two K and two V^T tiles in LDS.  bf16 at d = 128, b = 64 has two waves to a
-// workgroup, and with 64-key tiles (64 KiB) a CU's LDS holds two of them, one
-// wave per SIMD; 32-key tiles give two (12K tokens, 32/8 heads, sparse: 516
-// -> 434 us).  At d = 64 64-key tiles leave room for two waves per SIMD
-// anyway, and 32-key ones were slower at two, three and four waves (20K, b =
-// 64: 579 against 607, 608, 615 us; b = 128: 534 against 560-570).
+// two K and two V^T tiles in LDS.  At d = 128, b = 64 there are two waves to a
+// workgroup, and with 64-key tiles (bf16 64 KiB, fp32 128 KiB) a CU's LDS
+// holds two of them (fp32: one), one wave per SIMD (half); 32-key tiles give
+// twice that (sparse, 32/8 heads: bf16 12K 516 -> 434 us, fp32 8K 1561 -> 985
+// us).  bf16 at d = 64: 64-key tiles leave room for two waves per SIMD anyway,
+// and 32-key ones were slower at two, three and four waves (20K, b = 64: 579
+// against 607, 608, 615 us; b = 128: 534 against 560-570).  fp32 at d = 64, b =
+// 128: as fast either way, but 64-key steps spill registers.  fp32 with d = b:
+// 32-key steps were slower (d 64 dense 5K 347 -> 382 us, d 128 8K 917 -> 1009).
 template <typename T, int D, int B>
-constexpr int sub_keys() { return sizeof(T) == 2 && D == 128 && B == 64 ? 32 : 64; }
+constexpr int sub_keys() {
+    return (D == 128 && B == 64) || (sizeof(T) == 4 && D == 64 && B == 128) ? 32 : 64;
+}
 
 // Tile layout of a sub-block (in the copy and in LDS alike, so that a tile
 // moves to LDS as one contiguous run): lines of D elements (see line_pos).
@@ -183,7 +188,7 @@ struct AttnCfg {
     static constexpr int STAGE = K_ELEMS + V_ELEMS;
     static constexpr int VPT = SUB / V / NTH;          // 16-byte vectors per thread per sub-block
     // Waves per SIMD the LDS of one CU (160 KiB) leaves room for, capped at
-    // 2: the kernel's register budget.  fp32 at d = 128, and at b = 64, is
+    // 2: the kernel's register budget.  fp32 with d = b, and at d = 128, is
     // held to one wave per SIMD by LDS.
     static constexpr int LDS_BYTES = 2 * STAGE * (int)sizeof(T) + 16;
     static constexpr int WAVES_PER_SIMD_LDS = (160 * 1024 / LDS_BYTES) * (NTH / 64) / 4;
