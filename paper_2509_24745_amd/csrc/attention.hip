@@ -191,8 +191,18 @@ struct AttnCfg {
     // 2: the kernel's register budget.  fp32 with d = b, and at d = 128, is
     // held to one wave per SIMD by LDS.
     static constexpr int LDS_BYTES = 2 * STAGE * (int)sizeof(T) + 16;
-    static constexpr int WAVES_PER_SIMD_LDS = (160 * 1024 / LDS_BYTES) * (NTH / 64) / 4;
-    static constexpr int MIN_WAVES = WAVES_PER_SIMD_LDS < 1 ? 1 : (WAVES_PER_SIMD_LDS > 2 ? 2 : WAVES_PER_SIMD_LDS);
+    // The same with G groups of waves to a workgroup (see attn_kernel).
+    static constexpr int lds_bytes(int G) { return G * (LDS_BYTES + B * 8); }
+    static constexpr int min_waves(int G) {
+        const int n = (160 * 1024 / lds_bytes(G)) * (G * NTH / 64) / 4;
+        return n < 1 ? 1 : (n > 2 ? 2 : n);
+    }
+    // Two groups fit a CU's LDS (all but fp32 at d = b = 128) and pay: bf16 at
+    // d = b = 128 already keeps a CU's matrix pipes busy with one four-wave
+    // workgroup's 32 rows a wave, and lists are short in 128-key blocks
+    // (sparse 32 heads 512: 17.5 -> 19.9 us, 1K: 23.7 -> 26.2, 8 heads 4K: 43.8
+    // -> 44.0 us; only dense 1K gained, 48.3 -> 39.4 us).
+    static constexpr bool CAN_SPLIT = lds_bytes(2) <= 160 * 1024 && !(sizeof(T) == 2 && D == 128 && B == 128);
 };
 
 // Direct global -> LDS copy of one kvb sub-block (a K tile, then a V^T
@@ -297,18 +307,34 @@ __device__ __forceinline__ float prob_sum(const bf16x8 (*pf)[2]) {
     return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
+// Accumulators of group 1 on their way to group 0, through the tiles: register
+// quad rg of wave w is a 1 KiB run, 16 bytes a lane, the quads of output tile
+// dt at the end of array dt of the four that hold both groups' tiles (`slot`:
+// group 0's).  At d = 128 that is group 1's tile alone.
+template <typename T, int D, int B>
+__device__ __forceinline__ f32x4* acc_quad(const LdsSlots<T>& slot, int w, int dt, int rg, int lane) {
+    constexpr int RUNS = 2 * AttnCfg<T, D, B>::K_ELEMS * (int)sizeof(T) / 1024;   // per array
+    constexpr int NEED = B / 32 * 4;
+    static_assert(AttnCfg<T, D, B>::K_ELEMS == AttnCfg<T, D, B>::V_ELEMS, "equal tiles");
+    static_assert(NEED <= (D == 128 ? RUNS / 2 : RUNS), "O fits the tiles");
+    T* tiles = dt == 0 ? slot.k0 : dt == 1 ? slot.k1 : dt == 2 ? slot.v0 : slot.v1;
+    return reinterpret_cast<f32x4*>(tiles) + (RUNS - NEED + w * 4 + rg) * 64 + lane;
+}
+
 // One work item: query block m of query head i.  Every wave of the
 // workgroup calls it with the same (m, i); it starts and ends with no copy
 // in flight, and the caller's barrier separates it from the previous item's
-// LDS reads.
-template <typename T, int D, int B, bool DENSE>
+// LDS reads.  G = 2: the second group of waves (grp 1, with tiles of its own)
+// walks the second half of the list, and group 0 joins the two.
+template <typename T, int D, int B, bool DENSE, int G>
 __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ q,
                                          const T* __restrict__ kvb,
                                          const int* __restrict__ block_count,
                                          const int* __restrict__ block_index,
                                          T* __restrict__ out, float* __restrict__ lse,
                                          const int m, const int i,
-                                         const LdsSlots<T>& slot) {
+                                         const LdsSlots<T>& slot, const int grp,
+                                         float2* __restrict__ ml) {
     typedef AttnCfg<T, D, B> C;
     typedef typename FragOf<T>::type Frag;
     typedef SubTileDma<T, D, C::KT, C::NTH / 64> Dma;
@@ -316,19 +342,22 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
     constexpr int DT = D / 32;   // output tiles along d
     constexpr int KS = D / 16;   // k steps of Q K^T
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, lc = lane & 31;
+    const int tid = threadIdx.x - grp * C::NTH, lane = tid & 63, w = tid >> 6, h = lane >> 5, lc = lane & 31;
     const int kvh = i / sh.rep;
     const int n_tok = sh.n;
     // counts and indices are clamped to the causal range, so malformed caller
     // lists give wrong values but never an out-of-bounds access
-    const int cnt = DENSE ? (m + 1) : min(block_count[(int64_t)i * sh.mq + m], m + 1);
-    const int* list = DENSE ? nullptr : block_index + ((int64_t)i * sh.mq + m) * sh.mq;
+    const int cnt_all = DENSE ? (m + 1) : min(block_count[(int64_t)i * sh.mq + m], m + 1);
+    // this group's entries of the list: [first, first + cnt), cnt <= per
+    const int per = (cnt_all + G - 1) / G, first = grp * per;
+    const int cnt = G == 1 ? cnt_all : min(max(cnt_all - first, 0), per);
+    const int* list = DENSE ? nullptr : block_index + ((int64_t)i * sh.mq + m) * sh.mq + first;
     const int qtok = m * B + 32 * w + lc;
     const bool qvalid = qtok < n_tok;
     const int qlim = min(qtok, n_tok - 1);   // last key this row may see
 
-    if (cnt <= 0) {
-        if (qvalid) {
+    if (cnt_all <= 0) {   // the whole workgroup
+        if (grp == 0 && qvalid) {
             T* orow = out + (int64_t)qtok * sh.o_tok + (int64_t)i * sh.o_head;
             // lane half h zeroes elements [h D/2, (h+1) D/2); a rolled loop,
             // so that no per-lane address stays live across work items
@@ -355,7 +384,7 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
     // return would force every LDS wait to drain completely.
     int lst_base = -64, lst = 0;
     auto block_of = [&](int it) -> int {
-        if (DENSE) return it;
+        if (DENSE) return G == 1 ? it : min(first + it, m);
         const int c0 = it & ~63;
         if (c0 != lst_base) {
             lst_base = c0;
@@ -387,6 +416,8 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[dt] = zero16();
 
+    // (a group without entries goes through the prologue on some block of the
+    // causal range and drops what it finds)
     const int steps = cnt * C::NSUB;
     auto nb_of_step = [&](int j, int nb_prev) {
         return (j % C::NSUB == 0) ? block_of(j / C::NSUB) : nb_prev;
@@ -635,14 +666,46 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
         if (st + 1 < steps) step(s_alt, s_cur, st + 1);
     }
 
-    const float l_tot = halves_sum(l_run);
+    float l_tot = halves_sum(l_run);
+    if constexpr (G == 2) {
+        // the barriers of the longer group's remaining steps, and one more:
+        // nobody reads a tile any longer
+        for (int st = steps; st <= per * C::NSUB; ++st) __syncthreads();
+        const LdsSlots<T> all{slot.k0 - grp * C::K_ELEMS, slot.k1 - grp * C::K_ELEMS,
+                              slot.v0 - grp * C::V_ELEMS, slot.v1 - grp * C::V_ELEMS};
+        if (grp) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg)
+                    *acc_quad<T, D, B>(all, w, dt, rg, lane) = f32x4{
+                        o[dt][4 * rg], o[dt][4 * rg + 1], o[dt][4 * rg + 2], o[dt][4 * rg + 3]};
+            if (h == 0) ml[32 * w + lc] = steps ? make_float2(m_run, l_tot) : make_float2(kNegInf, 0.f);
+        }
+        __syncthreads();
+        if (grp) return;
+        const float2 x = ml[32 * w + lc];
+        const float top = fmaxf(m_run, x.x);   // finite: group 0 has an entry, and a row sees a key of it
+        const float a = m_run == kNegInf ? 0.f : fast_exp2(m_run - top);
+        const float b = x.x == kNegInf ? 0.f : fast_exp2(x.x - top);
+        m_run = top;
+        l_tot = l_tot * a + x.y * b;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const f32x4 y = *acc_quad<T, D, B>(all, w, dt, rg, lane);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) o[dt][4 * rg + u] = o[dt][4 * rg + u] * a + y[u] * b;
+            }
+    }
     const float inv = 1.f / l_tot;
     if constexpr (sizeof(T) == 2 && D == 128 && B == 128) {
         // O through LDS: the wave's 32 x D tile is written to the K slots
         // (free once every wave is done with the last step) and read back as
         // 16-byte row chunks, so that each store writes whole 128-byte lines
         static_assert(2 * 32 * D <= C::K_ELEMS, "two waves' O tiles per K slot");
-        __syncthreads();
+        if (G == 1) __syncthreads();
         T* ot = (w < 2 ? slot.k(0) : slot.k(1)) + (w & 1) * 32 * D;
         // new to the optimizer: no address of the epilogue is an item-loop
         // invariant kept in a register through the steps
@@ -699,8 +762,13 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
 // hands workgroups to the shader engines of an XCD in a fixed rotation, so a
 // grid of one workgroup per item lets the engines that receive the long items
 // hold back all the others.
-template <typename T, int D, int B, bool DENSE>
-__global__ __launch_bounds__(2 * B, (AttnCfg<T, D, B>::MIN_WAVES)) void attn_kernel(Shape sh, const T* __restrict__ q,
+//
+// G = 2, for launches of few items (see attn_d), which last as long as their
+// longest list: a workgroup of twice the waves and tiles gives each item's
+// list to two groups of waves, half of the entries each, and joins them
+// through LDS.  fp32 2K prefill, 8/2 heads, d 64 b 64: 54.9 -> 47.0 us, same box.
+template <typename T, int D, int B, bool DENSE, int G>
+__global__ __launch_bounds__(2 * B * G, (AttnCfg<T, D, B>::min_waves(G))) void attn_kernel(Shape sh, const T* __restrict__ q,
                                                         const T* __restrict__ kvb,
                                                         const int* __restrict__ block_count,
                                                         const int* __restrict__ block_index,
@@ -708,11 +776,16 @@ __global__ __launch_bounds__(2 * B, (AttnCfg<T, D, B>::MIN_WAVES)) void attn_ker
                                                         float* __restrict__ lse,
                                                         int* __restrict__ queue) {
     typedef AttnCfg<T, D, B> C;
-    __shared__ __attribute__((aligned(16))) T ks0[C::K_ELEMS];
-    __shared__ __attribute__((aligned(16))) T ks1[C::K_ELEMS];
-    __shared__ __attribute__((aligned(16))) T vs0[C::V_ELEMS];
-    __shared__ __attribute__((aligned(16))) T vs1[C::V_ELEMS];
-    const LdsSlots<T> slot{ks0, ks1, vs0, vs1};
+    __shared__ __attribute__((aligned(16))) T ks0[G * C::K_ELEMS];
+    __shared__ __attribute__((aligned(16))) T ks1[G * C::K_ELEMS];
+    __shared__ __attribute__((aligned(16))) T vs0[G * C::V_ELEMS];
+    __shared__ __attribute__((aligned(16))) T vs1[G * C::V_ELEMS];
+    __shared__ float2 ml[G == 1 ? 1 : B];
+    // the same for every lane of a wave, and known to be: the groups' step
+    // counts, and with them their barriers, differ
+    const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / C::NTH);
+    const LdsSlots<T> slot{ks0 + grp * C::K_ELEMS, ks1 + grp * C::K_ELEMS, vs0 + grp * C::V_ELEMS,
+                           vs1 + grp * C::V_ELEMS};
     __shared__ int next_item;
     const int per_queue = attn_items(sh) / kNumXcd, own = (int)gridDim.x / kNumXcd;
     // The first item of every workgroup is its own number's (the grid is a
@@ -749,7 +822,7 @@ __global__ __launch_bounds__(2 * B, (AttnCfg<T, D, B>::MIN_WAVES)) void attn_ker
         if (item < 0) break;
         int m, i;
         if (attn_item(sh, item, &m, &i))
-            attn_one<T, D, B, DENSE>(sh, q, kvb, block_count, block_index, out, lse, m, i, slot);
+            attn_one<T, D, B, DENSE, G>(sh, q, kvb, block_count, block_index, out, lse, m, i, slot, grp, ml);
         if (threadIdx.x < 64) {
             if (threadIdx.x == 0) pos = own + atomicAdd(queue + x * kQueueStride, 1);
             pos = __builtin_amdgcn_readfirstlane(pos);
@@ -805,25 +878,54 @@ static int resident_grid(const void* fn, int threads, int* grid) {
     return 0;
 }
 
+constexpr int kSplitItems = 256, kSplitRows = 8;
+
+template <typename T, int D, int B, bool DENSE, int G>
+static hipError_t attn_g(const Shape& s, const dim3& grid, const void* q, const void* kvb,
+                         const int* bc, const int* bi, void* out, float* lse, int* queue,
+                         hipStream_t st) {
+    hipLaunchKernelGGL((attn_kernel<T, D, B, DENSE, G>), grid, dim3(2 * B * G), 0, st, s,
+                       (const T*)q, (const T*)kvb, bc, bi, (T*)out, lse, queue);
+    return hipGetLastError();
+}
+
+template <typename T, int D, int B, bool DENSE>
+static hipError_t attn_d(const Shape& s, const void* q, const void* kvb, const int* bc,
+                         const int* bi, void* out, float* lse, int* queue, hipStream_t st) {
+    int g = 0;
+    // Lists are split while there are no more items than the MI355X has CUs,
+    // and at least kSplitRows block rows.  K/V copy and attention, sparse and
+    // dense, whole -> split: 256 items, 8 heads of 32 block rows, fp32 d 64
+    // b 64 51.4 -> 34.6 and 101.5 -> 62.2 us, fp32 d 128 b 64 89.7 -> 58.2 and
+    // 183 -> 110 us, bf16 d 128 b 64 27.4 -> 23.2 and 48.1 -> 35.0 us; 32 heads
+    // of 8 block rows, fp32 d 64 b 64 22.9 -> 19.5 and 40.7 -> 31.3 us, bf16 d 128
+    // b 64 17.5 -> 16.8 and 30.1 -> 25.3 us.  Up to 4 block rows the join takes
+    // what the shorter chain gives (bf16 d 128 b 64 dense 18.9 -> 21.3 us), and
+    // with 512 items in two workgroups per CU short lists lose (sparse 27.1 ->
+    // 28.4 us).  The items counted are the (head, row) pairs, so that no work
+    // order changes a result, and dense and sparse follow one rule.
+    if constexpr (AttnCfg<T, D, B>::CAN_SPLIT) {
+        if (s.mq >= kSplitRows && (int64_t)s.hq * s.mq <= kSplitItems) {
+            const int e = resident_grid((const void*)attn_kernel<T, D, B, DENSE, 2>, 4 * B, &g);
+            if (e) return (hipError_t)e;
+            return attn_g<T, D, B, DENSE, 2>(s, dim3((unsigned)std::min(g, attn_items(s))), q, kvb, bc,
+                                             bi, out, lse, queue, st);
+        }
+    }
+    const int e = resident_grid((const void*)attn_kernel<T, D, B, DENSE, 1>, 2 * B, &g);
+    if (e) return (hipError_t)e;
+    return attn_g<T, D, B, DENSE, 1>(s, dim3((unsigned)std::min(g, attn_items(s))), q, kvb, bc, bi,
+                                     out, lse, queue, st);
+}
+
 template <typename T, int D, int B>
 static hipError_t attn_t(const Shape& sh, bool dense, const void* q, const void* kvb,
                          const int* bc, const int* bi, void* out, float* lse, int* queue,
                          hipStream_t st) {
-    const void* fn = dense ? (const void*)attn_kernel<T, D, B, true>
-                           : (const void*)attn_kernel<T, D, B, false>;
-    int g = 0;
-    const int e = resident_grid(fn, 2 * B, &g);
-    if (e) return (hipError_t)e;
+    if (!dense) return attn_d<T, D, B, false>(sh, q, kvb, bc, bi, out, lse, queue, st);
     Shape s = sh;
-    if (dense) s.attn_order = sh.attn_order_dense;
-    const dim3 grid((unsigned)std::min(g, attn_items(s)));
-    if (dense)
-        hipLaunchKernelGGL((attn_kernel<T, D, B, true>), grid, dim3(2 * B), 0, st, s,
-                           (const T*)q, (const T*)kvb, bc, bi, (T*)out, lse, queue);
-    else
-        hipLaunchKernelGGL((attn_kernel<T, D, B, false>), grid, dim3(2 * B), 0, st, s,
-                           (const T*)q, (const T*)kvb, bc, bi, (T*)out, lse, queue);
-    return hipGetLastError();
+    s.attn_order = sh.attn_order_dense;
+    return attn_d<T, D, B, true>(s, q, kvb, bc, bi, out, lse, queue, st);
 }
 
 hipError_t launch_attention(const Shape& sh, bool dense, const void* q, const void* kvb,
