@@ -171,21 +171,22 @@ __device__ __forceinline__ float halves_max2(float a, float b) {
 
 // ---------------------------------------------------------------------------
 // a1: pooling.  One 256-thread workgroup per 256 (pooled row, 16-byte slice)
-// pairs; `blk` is the workgroup's index among the pooling workgroups.
+// pairs of one group; `blk` is the workgroup's index among the group's, so
+// that heads are the same for the whole workgroup, their addresses scalar,
+// and a KV head's slice is loaded once for the batch's query heads.  (One
+// index over all groups, divided per lane, and a K load per query head: estimate
+// call 128K 969 -> 962 us, 32K d 64 135 -> 132 us.  Pooling workgroups dealt
+// between those of mass_block: up to 9 % slower at 50K, as fast at best.)
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 __device__ __forceinline__ void pool_body(const Shape& sh, const T* __restrict__ q,
                                           const T* __restrict__ k, T* __restrict__ qg,
-                                          T* __restrict__ kg, int64_t blk) {
+                                          T* __restrict__ kg, int g, int blk) {
     constexpr int V = Vec16<T>::n;
     constexpr int SLICES = D / V;
-    const int64_t gid = blk * 256 + threadIdx.x;
-    const int64_t rows = (int64_t)sh.g * sh.np;
-    if (gid >= rows * SLICES) return;
-    const int slice = (int)(gid % SLICES);
-    const int64_t row = gid / SLICES;
-    const int g = (int)(row / sh.np);
-    const int tp = (int)(row % sh.np);
+    const int slice = threadIdx.x % SLICES;
+    const int tp = blk * (256 / SLICES) + threadIdx.x / SLICES;
+    if (tp >= sh.np) return;
     const int64_t t = (int64_t)tp * sh.s;
     float aq[V], ak[V];
 #pragma unroll
@@ -195,15 +196,25 @@ __device__ __forceinline__ void pool_body(const Shape& sh, const T* __restrict__
     // discards it), then added in ascending head order
     constexpr int kPoolBatch = 4;
     const int i0 = g * sh.gsize, i1 = i0 + sh.gsize;
+    const T* qrow = q + t * sh.q_tok + slice * V;
+    const T* krow = k + t * sh.kv_tok + slice * V;
     for (int ib = i0; ib < i1; ib += kPoolBatch) {
         uint4 qv[kPoolBatch], kv[kPoolBatch];
+        // a batch's heads of one KV head share its slice: one load
+        const int last = min(ib + kPoolBatch, i1) - 1;
+        const bool one_kv = ib / sh.rep == last / sh.rep;
 #pragma unroll
-        for (int u = 0; u < kPoolBatch; ++u) {
-            const int i = min(ib + u, i1 - 1);
-            qv[u] = *reinterpret_cast<const uint4*>(q + t * sh.q_tok + (int64_t)i * sh.q_head +
-                                                    slice * V);
-            kv[u] = *reinterpret_cast<const uint4*>(k + t * sh.kv_tok +
-                                                    (int64_t)(i / sh.rep) * sh.kv_head + slice * V);
+        for (int u = 0; u < kPoolBatch; ++u)
+            qv[u] = *reinterpret_cast<const uint4*>(qrow + (int64_t)min(ib + u, last) * sh.q_head);
+        if (one_kv) {
+            kv[0] = *reinterpret_cast<const uint4*>(krow + (int64_t)(ib / sh.rep) * sh.kv_head);
+#pragma unroll
+            for (int u = 1; u < kPoolBatch; ++u) kv[u] = kv[0];
+        } else {
+#pragma unroll
+            for (int u = 0; u < kPoolBatch; ++u)
+                kv[u] = *reinterpret_cast<const uint4*>(
+                    krow + (int64_t)(min(ib + u, last) / sh.rep) * sh.kv_head);
         }
 #pragma unroll
         for (int u = 0; u < kPoolBatch; ++u) {
@@ -616,7 +627,8 @@ __device__ __forceinline__ void mass_sum_body(const Shape& sh, const float2* __r
 // workgroups of the longer role come first).
 // ---------------------------------------------------------------------------
 struct EstGrid {
-    int pool;      // pooling workgroups
+    int pool;      // pooling workgroups: G x pool_per
+    int pool_per;  // per group
     int mblock;    // mass_block workgroups: nchunks x Hq
     int rowmax;    // est_rowmax workgroups: nbx x est_nc x G (of the band group)
     int nbx;       // 128-row bands of est_rowmax in the band group
@@ -642,7 +654,8 @@ __global__ __launch_bounds__(256, 2) void est_stage1_kernel(Shape sh, EstGrid eg
         mass_block_body<T, D, B>(sh, q, k, part, j % sh.nchunks, j / sh.nchunks);
         return;
     }
-    pool_body<T, D>(sh, q, k, qg, kg, j - eg.mblock);
+    const int jp = j - eg.mblock;
+    pool_body<T, D>(sh, q, k, qg, kg, jp / eg.pool_per, jp % eg.pool_per);
 }
 
 template <typename T, int D, int BP>
@@ -689,8 +702,9 @@ static EstGrid est_grid(const Shape& sh) {
     EstGrid e{};
     constexpr int kVec = 16;   // bytes per pooled slice
     const int esz = sh.dtype == 0 ? 2 : 4;
-    const int64_t slices = (int64_t)sh.g * sh.np * (sh.d * esz / kVec);
-    e.pool = (int)((slices + 255) / 256);
+    const int slices = sh.d * esz / kVec;
+    e.pool_per = (int)(((int64_t)sh.np * slices + 255) / 256);
+    e.pool = sh.g * e.pool_per;
     e.mblock = sh.nchunks * sh.hq;
     e.norm_per = (std::min(sh.b, sh.n) + 3) / 4;
     e.norm = sh.hq * e.norm_per;
