@@ -60,6 +60,7 @@
 // the per-(row, block) maxima they pass on need a bounded region (the mass
 // stages run with the first group).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -373,12 +374,28 @@ __device__ __forceinline__ void est_rowmax_body(const Shape& sh, const T* __rest
 // a3: row normalisers and the block max-pool in the log domain.
 // One 256-thread workgroup per (block row m, group g).
 // ---------------------------------------------------------------------------
+
+// Maximum over groups of W consecutive lanes (W = 4 .. 32), in every lane.
+template <int W>
+__device__ __forceinline__ float lanes_max(float v) {
+    auto dpp = [](float x, auto ctrl) {
+        const int i = __float_as_int(x);
+        return __int_as_float(__builtin_amdgcn_update_dpp(i, i, decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v = fmaxf(v, dpp(v, std::integral_constant<int, 0xB1>()));                        // quad_perm 1 0 3 2
+    v = fmaxf(v, dpp(v, std::integral_constant<int, 0x4E>()));                        // quad_perm 2 3 0 1
+    if constexpr (W >= 8) v = fmaxf(v, dpp(v, std::integral_constant<int, 0x141>())); // row_half_mirror
+    if constexpr (W >= 16) v = fmaxf(v, dpp(v, std::integral_constant<int, 0x140>())); // row_mirror
+    if constexpr (W >= 32) v = fmaxf(v, __shfl_xor(v, 16));
+    return v;
+}
+
 template <int BP>
 __device__ __forceinline__ void est_reduce_body(const Shape& sh, const float* __restrict__ rbm,
                                                 const float2* __restrict__ rowpart,
                                                 float* __restrict__ logA, int m, int g,
                                                 int64_t tri_base, int64_t tri_count) {
-    __shared__ float L[BP];
+    __shared__ __attribute__((aligned(16))) float L[BP];
     const int tid = threadIdx.x;
     const int r0 = m * BP;
     const int nr = min(BP, sh.np - r0);
@@ -424,6 +441,40 @@ __device__ __forceinline__ void est_reduce_body(const Shape& sh, const float* __
     __syncthreads();
     const float* base = rbm + ((int64_t)g * tri_count + tri_index(m, 0) - tri_base) * BP;
     float* out = logA + ((int64_t)g * sh.mq + m) * sh.mq;
+    if (nr == BP && sh.mq > 256) {
+        // Bound by its loads.  A wave takes 64 blocks at a time, G = BP / 4
+        // lanes to a block: its loads are whole contiguous KiB, kLoads of them
+        // in flight.  A lane keeps the maximum of the blocks of load lane % G.
+        // One lane to a block, below, reads 16 bytes of 64 lines at a time:
+        // estimate call 128K 969 -> 959 us, 50K stride 2 913 -> 905 us, 64K 456
+        // -> 452 us.  Up to 256 blocks (64 for each wave) there is one pass
+        // either way, and this one was up to 0.6 % slower (8K, 16K).
+        constexpr int G = BP / 4, PER = 64 / G, kLoads = G < 8 ? G : 8;
+        const int lane = tid & 63, sub = lane % G, grp = lane / G;
+        const f32x4 lr = *reinterpret_cast<const f32x4*>(L + 4 * sub);
+        for (int n0 = tid - lane; n0 < sh.mq; n0 += 256) {
+            const int n = n0 + sub * PER + grp;
+            float v = kNegInf;
+            if (n0 <= m) {
+                for (int u0 = 0; u0 < G; u0 += kLoads) {
+                    f32x4 x[kLoads];
+#pragma unroll
+                    for (int u = 0; u < kLoads; ++u)
+                        x[u] = *reinterpret_cast<const f32x4*>(
+                            base + (int64_t)min(n0 + (u0 + u) * PER + grp, m) * BP + 4 * sub);
+#pragma unroll
+                    for (int u = 0; u < kLoads; ++u) {
+                        const float t = lanes_max<G>(fmaxf(fmaxf(x[u][0] - lr[0], x[u][1] - lr[1]),
+                                                           fmaxf(x[u][2] - lr[2], x[u][3] - lr[3])));
+                        v = sub == u0 + u ? t : v;
+                    }
+                }
+                v = n <= m ? v * kLn2 : kNegInf;
+            }
+            if (n < sh.mq) out[n] = v;
+        }
+        return;
+    }
     for (int n = tid; n < sh.mq; n += 256) {
         float v = kNegInf;
         if (n <= m) {
