@@ -789,44 +789,34 @@ __global__ __launch_bounds__(2 * B * G, (AttnCfg<T, D, B>::min_waves(G))) void a
     __shared__ int next_item;
     const int per_queue = attn_items(sh) / kNumXcd, own = (int)gridDim.x / kNumXcd;
     // The first item of every workgroup is its own number's (the grid is a
-    // multiple of kNumXcd); the counters hand out the rest.  Own XCD's queue
-    // first; once it is empty, one load of all counters finds the next queue
-    // with items left (their shortest), so no XCD idles while another still
-    // has work, and a workgroup that finds none ends.  The counters only
-    // grow, so every workgroup gets there.  (With a ticket for the first item
-    // and one probe after the other of the empty queues every launch took 3 us
-    // longer: one 128-token block 13.3 against 10.0 us.)
-    int x = blockIdx.x % kNumXcd, pos = blockIdx.x / kNumXcd;
+    // multiple of kNumXcd); the counters hand out the rest, so a launch with
+    // no more items than workgroups touches none.  Own XCD's queue first; once
+    // it is empty, the other queues in turn (their remaining items are their
+    // shortest), so no XCD idles while another still has work.  Every probe of
+    // an empty queue moves on, so the loop ends after at most kNumXcd of them.
+    // (One load of all counters instead of the probes kept up to a thousand
+    // workgroups waiting at the end: bf16, 32/8 heads, sparse, 1024 workgroups,
+    // K/V copy and attention, probes against the load: d 64 b 64 1.5K 19.6
+    // against 31.3 us, 2.1K 31.1 against 42.5, 4173 53.0 against 63.0, 20K 552
+    // against 558; with 256 or 512 workgroups the load was up to 3 us faster.
+    // A ticket for the first item as well: 1-2 us slower.)
+    int x = blockIdx.x % kNumXcd, pos = blockIdx.x / kNumXcd, empty = 0;
     for (;;) {
-        if (threadIdx.x < 64) {   // wave 0
-            const int lane = threadIdx.x;
-            while (pos >= per_queue) {
-                int taken = per_queue;
-                if (lane < kNumXcd)
-                    taken = own + __hip_atomic_load(queue + lane * kQueueStride, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-                const unsigned left = (unsigned)__builtin_amdgcn_ballot_w64(taken < per_queue);
-                if (!left) break;
-                const unsigned turn = (left >> x | left << (kNumXcd - x)) & ((1u << kNumXcd) - 1u);
-                x = (x + __builtin_ctz(turn)) % kNumXcd;
-                if (lane == 0) pos = own + atomicAdd(queue + x * kQueueStride, 1);
-                pos = __builtin_amdgcn_readfirstlane(pos);
-            }
-            if (lane == 0) next_item = pos < per_queue ? x + kNumXcd * pos : -1;
+        if (pos < per_queue) {
+            int m, i;
+            if (attn_item(sh, x + kNumXcd * pos, &m, &i))
+                attn_one<T, D, B, DENSE, G>(sh, q, kvb, block_count, block_index, out, lse, m, i, slot, grp, ml);
+            if (own == per_queue) break;
+        } else {
+            if (++empty == kNumXcd) break;
+            x = (x + 1) % kNumXcd;
         }
+        if (threadIdx.x == 0) next_item = own + atomicAdd(queue + x * kQueueStride, 1);
         // the barriers also keep the previous item's LDS reads ahead of the
         // next item's copies
         __syncthreads();
-        const int item = __builtin_amdgcn_readfirstlane(next_item);
+        pos = __builtin_amdgcn_readfirstlane(next_item);
         __syncthreads();
-        if (item < 0) break;
-        int m, i;
-        if (attn_item(sh, item, &m, &i))
-            attn_one<T, D, B, DENSE, G>(sh, q, kvb, block_count, block_index, out, lse, m, i, slot, grp, ml);
-        if (threadIdx.x < 64) {
-            if (threadIdx.x == 0) pos = own + atomicAdd(queue + x * kQueueStride, 1);
-            pos = __builtin_amdgcn_readfirstlane(pos);
-        }
     }
 }
 
