@@ -73,7 +73,9 @@ extern "C" {
  * Supported: d in {64, 128}; b in {64, 128}; s in {1, 2, 4} with b/s >= 16;
  * Hq <= 4096; Hq % Hkv == 0; Hq % G == 0; Nk <= 8192.  bf16 problems compute products on
  * bf16 MFMA with fp32 accumulation; fp32 problems too, with every operand
- * split exactly into three bf16 terms (no less exact than fp32 products).
+ * split into three bf16 terms (exactly for magnitudes from 2^-110 up, within
+ * 2^-134 below) and six of the nine products of two operands added up: what is
+ * left out of a product is below 2^-23 of it.
  */
 typedef struct proxyattn_problem {
     uint32_t struct_size;      /* = sizeof(proxyattn_problem) */

@@ -374,7 +374,7 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
     {
         const T* qrow = q + (int64_t)min(qtok, n_tok - 1) * sh.q_tok + (int64_t)i * sh.q_head;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = operand(load_frag<T>(qrow + 16 * ks + 8 * h));
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = query_operand(load_frag<T>(qrow + 16 * ks + 8 * h));
     }
 
     const T* kvbase = kvb + (int64_t)kvh * sh.mq * (2 * B * D);
@@ -407,7 +407,7 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
         for (int kt = 0; kt < NT; ++kt) {
             acc[kt] = zero16();
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) mma(acc[kt], operand(kfrag(kt_, kt, ks)), qf[ks]);
+            for (int ks = 0; ks < KS; ++ks) mma(acc[kt], key_operand(kfrag(kt_, kt, ks)), qf[ks]);
         }
     };
 
@@ -619,13 +619,13 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
             Frag f[NF];
             f[0] = frag(0);
             f[1] = frag(1);
-            Op cur = operand(f[0]);
+            Op cur = key_operand(f[0]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < NF; ++j) {
                 Op nxt = cur;
                 if (j + 2 < NF) f[j + 2] = frag(j + 2);
-                if (j + 1 < NF) nxt = operand(f[j + 1]);
+                if (j + 1 < NF) nxt = key_operand(f[j + 1]);
                 if (j < NQ) {
                     mma(sn[j % NT], cur, qf[j / NT]);
 #pragma unroll
@@ -635,14 +635,14 @@ __device__ __forceinline__ void attn_one(const Shape& sh, const T* __restrict__ 
                         pf[kt][r >> 3][r & 7] = pr;
                         ps[r & 3] += pr;
                     }
-                    if (j == NQ - 1) pop[0] = operand(pf[0][0]);
+                    if (j == NQ - 1) pop[0] = prob_operand(pf[0][0]);
                 } else {
                     const int p = j - NQ, g = p / DT;
                     mma(o[p % DT], cur, pop[g]);
                     if (g + 1 < 2 * NT) {
 #pragma unroll
                         for (int u = 0; u < 4 / DT; ++u)
-                            split3_pair(pop[g + 1], pf[(g + 1) / 2][(g + 1) % 2], p % DT * (4 / DT) + u);
+                            split3_pair<true, false>(pop[g + 1], pf[(g + 1) / 2][(g + 1) % 2], p % DT * (4 / DT) + u);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);

@@ -70,26 +70,54 @@ __device__ __forceinline__ void mma(f32x16& acc, const bf16x8& a, const bf16x8& 
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
 }
 
-// fp32 operands as three bf16 terms: x = hi + mid + lo exactly (hi the top 8
-// significant bits by truncation, so that no finite x overflows; mid and lo
-// by rounding what is left).  A product keeps six of the nine terms: the
-// others are below 2^-24 of it.  Six bf16 MFMAs of 16 k each take 192 cycles
-// where eight fp32 MFMAs of 2 k took 512, and round the accumulator six times
-// instead of eight: against 64 bits the error is 0.7-0.8 of the fp32 MFMAs'
-// (attention outputs 1.2e-6 against 1.5e-6 at 8K; scores 7.4e-8 against
-// 8.4e-8).  Sparse attention 8K, 32/8 heads, d 128: 1340 -> 911 us, dense d 64
-// b 64 5K: 543 -> 347 us, estimate 8K: 128 -> 96 us.
+// fp32 operands as three bf16 terms, x = hi + mid + lo: hi the top 8 significant
+// bits, by truncation (no finite x overflows, and one permute makes two) or, with
+// NEAR, to nearest; mid and lo by rounding what is left.  The sum is exact for
+// |x| >= 2^-110; below, bits under bf16's smallest denormal go, 2^-134 at most.
+// |mid| <= 2^-7 and |lo| <= 2^-16 of x's power of two with hi truncated, half of
+// each with hi to nearest, so the three products of nine that are left out stay
+// below 2^-23 of x y where one operand's hi is to nearest (2^-22 where neither
+// is): queries and probabilities are rounded, keys and values, which the inner
+// loops split, truncated.  Rounding those too takes two
+// more clamps a pair and 6-8 % more time (8K sparse, d 128: 927 -> 993 us), the
+// two next products in their place 12-16 %, for errors against 64 bits that are
+// the same on the timed cases.
+// Six bf16 MFMAs of 16 k each take 192 cycles where eight fp32 MFMAs of 2 k took
+// 512, and round the accumulator six times instead of eight, but by truncation.
+// Errors against 64 bits, fp32 MFMAs -> split: attention outputs 1.08e-6 ->
+// 8.5e-7 (3K, d 128) and 8.8e-7 -> 6.4e-7 (2K, d 64), block scores 1.08e-7 ->
+// 9.5e-8 (4K), means of 24 inputs; a dot product of 64 normal deviates, in units
+// of 2^-24 of its absolute sum, largest 2.5 -> 2.3, rms 0.47 -> 0.37; a single
+// product, largest 1.6 -> 2.8 (6.3 with both operands truncated), rms 0.60 -> 0.72.
+// Sparse attention 8K, 32/8 heads, d 128: 1340 -> 911 us, dense d 64 b 64 5K: 543
+// -> 347 us, estimate 8K: 128 -> 96 us.
 struct Split3 {
     bf16x8 hi, mid, lo;
 };
-// Elements 2 j and 2 j + 1.
+// Elements 2 j and 2 j + 1.  CLAMP keeps a value that would round past the
+// largest bf16 at it.
+template <bool NEAR, bool CLAMP>
 __device__ __forceinline__ void split3_pair(Split3& s, const f32x8& x, int j) {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const uint32_t a = __float_as_uint(x[2 * j]), b = __float_as_uint(x[2 * j + 1]);
-    const bf16x2 hi = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(b, a, 0x07060302u));
-    const f32x2 r = {x[2 * j] - __uint_as_float(a & 0xffff0000u),
-                     x[2 * j + 1] - __uint_as_float(b & 0xffff0000u)};
+    const float xa = x[2 * j], xb = x[2 * j + 1];
+    const uint32_t a = __float_as_uint(xa), b = __float_as_uint(xb);
+    bf16x2 hi;
+    uint32_t ha, hb;
+    if constexpr (NEAR) {
+        const float top = CLAMP ? __uint_as_float(0x7f7f0000u) : 0.f;
+        const f32x2 c = {CLAMP ? __builtin_amdgcn_fmed3f(xa, -top, top) : xa,
+                         CLAMP ? __builtin_amdgcn_fmed3f(xb, -top, top) : xb};
+        hi = __builtin_convertvector(c, bf16x2);
+        const uint32_t h = __builtin_bit_cast(uint32_t, hi);
+        ha = h << 16;
+        hb = h & 0xffff0000u;
+    } else {
+        hi = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(b, a, 0x07060302u));
+        ha = a & 0xffff0000u;
+        hb = b & 0xffff0000u;
+    }
+    const f32x2 r = {xa - __uint_as_float(ha), xb - __uint_as_float(hb)};
     const bf16x2 mid = __builtin_convertvector(r, bf16x2);
     const uint32_t m = __builtin_bit_cast(uint32_t, mid);
     const f32x2 t = {r[0] - __uint_as_float(m << 16), r[1] - __uint_as_float(m & 0xffff0000u)};
@@ -101,10 +129,11 @@ __device__ __forceinline__ void split3_pair(Split3& s, const f32x8& x, int j) {
     s.lo[2 * j] = lo[0];
     s.lo[2 * j + 1] = lo[1];
 }
+template <bool NEAR, bool CLAMP>
 __device__ __forceinline__ Split3 split3(const f32x8& x) {
     Split3 s;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) split3_pair(s, x, j);
+    for (int j = 0; j < 4; ++j) split3_pair<NEAR, CLAMP>(s, x, j);
     return s;
 }
 // The six products, smallest first.
@@ -117,11 +146,16 @@ __device__ __forceinline__ void mma(f32x16& acc, const Split3& a, const Split3& 
     mma(acc, a.hi, b.hi);
 }
 
-// Fragments as the MFMAs take them: bf16 as they are, fp32 split.
+// Fragments as the MFMAs take them: bf16 as they are, fp32 split.  One operand
+// of every product is a key or value, the other a query or a probability
+// (at most 2^8: nothing to clamp).
 template <typename T> struct OperandOf { typedef bf16x8 type; };
 template <> struct OperandOf<float> { typedef Split3 type; };
-__device__ __forceinline__ bf16x8 operand(const bf16x8& f) { return f; }
-__device__ __forceinline__ Split3 operand(const f32x8& f) { return split3(f); }
+__device__ __forceinline__ bf16x8 key_operand(const bf16x8& f) { return f; }
+__device__ __forceinline__ Split3 key_operand(const f32x8& f) { return split3<false, false>(f); }
+__device__ __forceinline__ bf16x8 query_operand(const bf16x8& f) { return f; }
+__device__ __forceinline__ Split3 query_operand(const f32x8& f) { return split3<true, true>(f); }
+__device__ __forceinline__ Split3 prob_operand(const f32x8& f) { return split3<true, false>(f); }
 
 template <typename T>
 __device__ __forceinline__ typename FragOf<T>::type load_frag(const T* p) {

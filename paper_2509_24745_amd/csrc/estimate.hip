@@ -124,8 +124,8 @@ __device__ __forceinline__ void step_scores(f32x16 (&acc)[2], const T* tile,
     acc[1] = zero16();
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
-        mma(acc[0], operand(lines.frag(tile, 16 * ks)), qf[ks]);
-        mma(acc[1], operand(lines.frag(tile + 32 * D, 16 * ks)), qf[ks]);
+        mma(acc[0], key_operand(lines.frag(tile, 16 * ks)), qf[ks]);
+        mma(acc[1], key_operand(lines.frag(tile + 32 * D, 16 * ks)), qf[ks]);
     }
 }
 
@@ -286,7 +286,7 @@ __device__ __forceinline__ void est_rowmax_body(const Shape& sh, const T* __rest
     {
         const T* qrow = qg + ((int64_t)g * np + min(row, np - 1)) * D;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = operand(load_frag<T>(qrow + 16 * ks + 8 * h));
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = query_operand(load_frag<T>(qrow + 16 * ks + 8 * h));
     }
     LaneLines<T, D> lines(lc, h);
 
@@ -532,7 +532,7 @@ __device__ __forceinline__ void mass_block_body(const Shape& sh, const T* __rest
     {
         const T* qrow = q + (int64_t)min(t, n - 1) * sh.q_tok + (int64_t)i * sh.q_head;
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = operand(load_frag<T>(qrow + 16 * ks + 8 * h));
+        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = query_operand(load_frag<T>(qrow + 16 * ks + 8 * h));
     }
     LaneLines<T, D> lines(lc, h);
     float2* prow = part + ((int64_t)i * B + rl) * sh.mq;
