@@ -115,13 +115,28 @@ struct StepCopy {
 };
 
 // Scores of one step, transposed (64 keys x 32 queries of one wave): lane
-// (lc, h) receives the keys 32 kt + c_row(r, h) of query lc.
+// (lc, h) receives the keys 32 kt + c_row(r, h) of query lc.  `half`: no query
+// of the wave sees a key of the second tile.  fp32 then leaves it out (its
+// scores are -inf): up to 128 tokens a launch lasts as long as one step, and
+// most of it is the tiles' splits and MFMAs.  Estimate call, 8/2 heads, d 128
+// b 64, both tiles against this: 16 tokens 18.0 -> 15.0 us, 33 18.7 -> 17.1, 64
+// 19.3 -> 17.8, 128 19.7 -> 18.0 (32-key steps 14.2, 17.2, 18.0, 18.4); longer
+// ones -2 to +0.5 %.  bf16 gained 0.2 us there and at d 64 b 64 lost 4-7 % at 8K
+// (stride 1, 32 heads 61.7 -> 66.0 us).
 template <typename T, int D>
 __device__ __forceinline__ void step_scores(f32x16 (&acc)[2], const T* tile,
                                             const LaneLines<T, D>& lines,
-                                            const typename OperandOf<T>::type* qf) {
+                                            const typename OperandOf<T>::type* qf, bool half) {
     acc[0] = zero16();
     acc[1] = zero16();
+    if (sizeof(T) == 4 && half) {
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+            mma(acc[0], key_operand(lines.frag(tile, 16 * ks)), qf[ks]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[1][r] = kNegInf;
+        return;
+    }
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
         mma(acc[0], key_operand(lines.frag(tile, 16 * ks)), qf[ks]);
@@ -321,8 +336,8 @@ __device__ __forceinline__ void est_rowmax_body(const Shape& sh, const T* __rest
         if (st < s1) copy.issue(st + 1, next);
         if (st > ws1) return;
         f32x16 acc[2];
-        step_scores<T, D>(acc, cur, lines, qf);
         const int k0 = st * kStepKeys;
+        step_scores<T, D>(acc, cur, lines, qf, k0 + 32 > row0 + 31);
         if (k0 + kStepKeys - 1 > row0) step_mask(acc, row - k0, h);
         // raw maxima (the scale is positive, so it commutes with max)
         const float a0 = max8(acc[0], 0), a1 = max8(acc[0], 8);
@@ -523,6 +538,7 @@ __device__ __forceinline__ void mass_block_body(const Shape& sh, const T* __rest
     const int rl = 32 * w + lc, t = t0 + rl;
     const bool wave_on = 32 * w < nrows;
     const int wave_first_t = t0 + 32 * w;
+    const int wave_last_t = t0 + min(32 * w + 31, nrows - 1);
     const int key0 = c * sh.mass_chunk, key1 = min(key0 + sh.mass_chunk, n);
     const int s0 = key0 / kStepKeys, s1 = (key1 - 1) / kStepKeys;
 
@@ -554,8 +570,8 @@ __device__ __forceinline__ void mass_block_body(const Shape& sh, const T* __rest
         if (st < s1) copy.issue(st + 1, next);
         if (!wave_on) return;
         f32x16 acc[2];
-        step_scores<T, D>(acc, cur, lines, qf);
         const int k0 = st * kStepKeys;
+        step_scores<T, D>(acc, cur, lines, qf, k0 + 32 > wave_last_t);
         // only steps reaching past the wave's first row need the causal mask
         if (k0 + kStepKeys - 1 > wave_first_t) step_mask(acc, t - k0, h);
         const float tm = halves_max(fmaxf(fmaxf(max8(acc[0], 0), max8(acc[0], 8)),
