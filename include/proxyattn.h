@@ -226,7 +226,11 @@ int proxyattn_select_topk(const proxyattn_problem* p, const float* block_logscor
  * order but must hold distinct blocks within 0..m, with 1 <= count <= m+1
  * (the lists proxyattn_select_budget writes satisfy this; a row with count 0
  * gets out = 0 and lse = -inf; out-of-range entries are clamped, never read
- * out of bounds).  Blocks are accumulated in list order.
+ * out of bounds).  Blocks are accumulated in list order; where a problem has
+ * few (head, block row) pairs, the two halves of a list, each in list order,
+ * and then their sums.  Which of the two depends on the problem's sizes alone
+ * (Hq, N, d, b, dtype), so the last bits of a head's output can differ between
+ * a layer and a shard of its heads.
  *  out: [N][Hq][d] in the problem's dtype (o strides).
  *  lse: [Hq][N] fp32 natural-log row log-sum-exp, or NULL.
  *  workspace: as for proxyattn_estimate.  The call first copies K and V into
@@ -241,7 +245,7 @@ int proxyattn_block_sparse_prefill(const proxyattn_problem* p, const void* q, co
 /*
  * The attention kernels read K and V from a blocked copy made once per K/V:
  * for every KV head and key block, its keys and its values transposed, cut
- * into sub-blocks of 64 keys that are each one contiguous chunk (rows past N
+ * into sub-blocks of 64 or 32 keys that are each one contiguous chunk (rows past N
  * are zero).  Callers that run several attention calls on the same K and V
  * (the sparse path and its dense baseline, several thresholds) make the copy
  * once with proxyattn_prepare_kv and pass it to the _blocked calls below.

@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 
 from oracle import check as C
 from oracle import proxyattn_oracle as O
-from paper_2509_24745_amd.synth import WORKLOADS
+from paper_2509_24745_amd.synth import WORKLOADS, Structure, Workload
 from tests.test_gpu_parity import LOGA_TOL, MASS_RTOL, _gpu
 
 pytestmark = pytest.mark.gpu
@@ -60,3 +60,39 @@ def test_head_shards_reproduce_the_whole_layer(parts):
         print(f"\n[{parts} parts, part {s}] |dlogA|={dla:.2e} |dmass|/rows={dm:.2e} "
               f"ambiguous heads={len(rep.ambiguous_heads)} rows={rep.ambiguous_rows}; "
               f"equal row counts {same}/{part['block_count'].size}", flush=True)
+
+
+def test_shards_across_the_split_line():
+    """The attention kernel splits lists between two wave groups in layers of
+    at most 256 (head, block row) items, so a head's bits are those of the
+    whole layer only where both layers are on one side of that line: 32 heads
+    of 32 rows, halves (512 items) bit for bit, quarters (256, split) to the
+    bars of test_gpu_tiles.py, which either side meets against 64 bits (so
+    their difference meets twice those); and quarters bit for bit among
+    smaller parts, which are split too."""
+    U = _gpu()
+    wl = Workload(name="t", seq_len=32 * 64 - 5, num_q_heads=32, num_kv_heads=8, head_dim=64,
+                  block_size=64, num_proxy_groups=8, stride=4, dtype="fp32", seed=3,
+                  structure=Structure(rank=8, hot_blocks=1))
+    q, k, v = U.inputs(wl)
+    bc, bi = O.full_causal_lists(wl.seq_len, 32, 64)
+
+    def part(parts, s):
+        rq, rk = 32 // parts, 8 // parts
+        prob = U.problem_of(wl.replace(num_q_heads=rq, num_kv_heads=rk, num_proxy_groups=rk))
+        hs, ks = slice(s * rq, (s + 1) * rq), slice(s * rk, (s + 1) * rk)
+        out, lse = U.run_attention(prob, q[:, hs], k[:, ks], v[:, ks], bc[hs].copy(), bi[hs].copy())
+        return out, lse, hs
+
+    full, full_lse, _ = part(1, 0)
+    for s in range(2):
+        out, lse, hs = part(2, s)
+        assert np.array_equal(out, full[:, hs]) and np.array_equal(lse, full_lse[hs])
+    quarter, quarter_lse, _ = part(4, 0)
+    do = float(np.max(np.abs(quarter - full[:, :8])))
+    dl = float(np.max(np.abs(quarter_lse - full_lse[:8])))
+    print(f"\n[across the line] |dO|={do:.2e} |dlse|={dl:.2e}", flush=True)
+    assert do <= 2 * 3.2e-5 and dl <= 2 * 2e-5
+    for s in range(2):
+        out, lse, hs = part(8, s)
+        assert np.array_equal(out, quarter[:, hs]) and np.array_equal(lse, quarter_lse[hs])
