@@ -891,9 +891,16 @@ static hipError_t attn_d(const Shape& s, const void* q, const void* kvb, const i
     // of 8 block rows, fp32 d 64 b 64 22.9 -> 19.5 and 40.7 -> 31.3 us, bf16 d 128
     // b 64 17.5 -> 16.8 and 30.1 -> 25.3 us.  Up to 4 block rows the join takes
     // what the shorter chain gives (bf16 d 128 b 64 dense 18.9 -> 21.3 us), and
-    // with 512 items in two workgroups per CU short lists lose (sparse 27.1 ->
-    // 28.4 us).  The items counted are the (head, row) pairs, so that no work
-    // order changes a result, and dense and sparse follow one rule.
+    // so it does with lists of a few blocks on either side of the line (one
+    // head of 100 rows, fp32 d 128 b 64 18.4 -> 21.0 us, bf16 10.3 -> 12.0; at
+    // worst 28 heads of 9 rows, bf16 d 64 b 128, 16.6 -> 21.0 us), which the host
+    // cannot see.  Past 256 items, 257 to 512 of them, dense calls would gain
+    // up to 45 % (28 and 32 heads at b 128: -33 to +9 %), sparse ones lose as
+    // often as they gain: bf16 d 64 b 64 -24 to +18 %, d 128 b 64 -27 to +11 %,
+    // d 64 b 128 +9 to +61 %; fp32 d 64 b 64 -30 to +23 %, d 128 b 64 -36 to
+    // +41 %, d 64 b 128 -23 to +41 %.  The items counted are the (head, row) pairs,
+    // so that no work order changes a result, and dense and sparse follow one
+    // rule.
     if constexpr (AttnCfg<T, D, B>::CAN_SPLIT) {
         if (s.mq >= kSplitRows && (int64_t)s.hq * s.mq <= kSplitItems) {
             const int e = resident_grid((const void*)attn_kernel<T, D, B, DENSE, 2>, 4 * B, &g);
