@@ -186,7 +186,6 @@ struct AttnCfg {
     static constexpr int K_ELEMS = KT * D;             // K tile (swizzled rows)
     static constexpr int V_ELEMS = D * KT;             // V^T tile
     static constexpr int STAGE = K_ELEMS + V_ELEMS;
-    static constexpr int VPT = SUB / V / NTH;          // 16-byte vectors per thread per sub-block
     // Waves per SIMD the LDS of one CU (160 KiB) leaves room for, capped at
     // 2: the kernel's register budget.  fp32 with d = b, and at d = 128, is
     // held to one wave per SIMD by LDS.
