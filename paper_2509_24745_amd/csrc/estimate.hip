@@ -599,44 +599,57 @@ __device__ __forceinline__ void mass_block_body(const Shape& sh, const T* __rest
     flush();
 }
 
-// Row normalisers: one wave per last-block row, 4 rows per 256-thread
+// Row normalisers: W lanes per last-block row, 256 / W rows per 256-thread
 // workgroup (`rg`: the workgroup's index among the head's): the row's
 // log2-sum-exp over its visible blocks n <= t / b (block n holds key n b <= t,
-// so every one of them was written).
+// so every one of them was written).  A wave per row, or W = 8 up to 8 blocks:
+// the workgroups share a launch with est_rowmax, whose tiles let only two to
+// five of them on a CU, and layers of many heads have thousands.  Estimate
+// call of 128 tokens, 512/64 heads, d 128 b 128, 64 lanes a row -> 8: fp32 72.9
+// -> 35.7 us, bf16 41.5 -> 20.6 (with the smaller tiles of 32-key steps 63.6 and
+// 37.3); 8/2 heads and longer calls as fast either way.  The sums' order is the
+// same: lanes past the last block add 0.
+constexpr int kNormShortBlocks = 8;
+
+template <int W>
 __device__ __forceinline__ void mass_norm_body(const Shape& sh, const float2* __restrict__ part,
                                                float* __restrict__ lnorm, int i, int rg) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int sub = threadIdx.x % W;
     const int b = sh.b, mq = sh.mq;
     const int nrows = min(b, sh.n), t0 = sh.n - nrows;
-    const int r = rg * 4 + w;
-    if (r >= nrows) return;   // whole waves; no barrier follows
+    const int r = rg * (256 / W) + threadIdx.x / W;
+    if (r >= nrows) return;   // whole rows; no barrier follows
     const int nmax = (t0 + r) / b;
     const float2* pr = part + ((int64_t)i * b + r) * mq;
-    // a lane's blocks nb = lane, lane + 64, ... in increasing order, read
+    // a lane's blocks nb = sub, sub + W, ... in increasing order, read
     // kNormBatch at a time (all in flight together); selects, not branches,
     // so that each pair is one 8-byte load
-    constexpr int kNormBatch = 4;
+    constexpr int kNormBatch = W == 64 ? 4 : 1;
     float m = kNegInf, s = 0.f;
-    for (int nb0 = lane; nb0 <= nmax; nb0 += 64 * kNormBatch) {
+    for (int nb0 = sub; nb0 <= nmax; nb0 += W * kNormBatch) {
         float2 xs[kNormBatch];
 #pragma unroll
         for (int u = 0; u < kNormBatch; ++u) {
-            const int nb = nb0 + 64 * u;
+            const int nb = nb0 + W * u;
             xs[u] = pr[min(nb, nmax)];
         }
 #pragma unroll
         for (int u = 0; u < kNormBatch; ++u) {
             const float2 x = xs[u];
-            const bool use = nb0 + 64 * u <= nmax && x.x != kNegInf;
+            const bool use = nb0 + W * u <= nmax && x.x != kNegInf;
             const float mn = fmaxf(m, x.x);
             const float sn = (m == kNegInf ? 0.f : s * fast_exp2(m - mn)) + x.y * fast_exp2(x.x - mn);
             s = use ? sn : s;
             m = use ? mn : m;
         }
     }
-    const float M = wave_max(m);   // finite: block 0 is visible to every row
-    const float sv = wave_sum(m == kNegInf ? 0.f : s * fast_exp2(m - M));
-    if (lane == 0) lnorm[(int64_t)i * b + r] = M + log2f(sv);
+    float M = m;   // finite in the end: block 0 is visible to every row
+#pragma unroll
+    for (int o = W / 2; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    float sv = m == kNegInf ? 0.f : s * fast_exp2(m - M);
+#pragma unroll
+    for (int o = W / 2; o >= 1; o >>= 1) sv += __shfl_xor(sv, o);
+    if (sub == 0) lnorm[(int64_t)i * b + r] = M + log2f(sv);
 }
 
 // Block masses: 64 blocks per 256-thread workgroup (`chunk`), one per lane.
@@ -700,7 +713,7 @@ struct EstGrid {
     int rowmax;    // est_rowmax workgroups: nbx x est_nc x G (of the band group)
     int nbx;       // 128-row bands of est_rowmax in the band group
     int xb1;       // one past the group's last band (bands run longest first)
-    int norm;      // mass_norm workgroups: Hq x ceil(rows / 4) (first group only)
+    int norm;      // mass_norm workgroups: Hq x norm_per (first group only)
     int norm_per;  // per head
     int reduce;    // est_reduce workgroups: the group's block rows x G
     int m0, nm;    // the group's block rows [m0, m0 + nm)
@@ -741,7 +754,10 @@ __global__ __launch_bounds__(256, 2) void est_stage2_kernel(Shape sh, EstGrid eg
         return;
     }
     const int jn = j - eg.rowmax;
-    mass_norm_body(sh, part, lnorm, jn / eg.norm_per, jn % eg.norm_per);
+    if (sh.mq <= kNormShortBlocks)
+        mass_norm_body<8>(sh, part, lnorm, jn / eg.norm_per, jn % eg.norm_per);
+    else
+        mass_norm_body<64>(sh, part, lnorm, jn / eg.norm_per, jn % eg.norm_per);
 }
 
 template <int BP>
@@ -773,7 +789,8 @@ static EstGrid est_grid(const Shape& sh) {
     e.pool_per = (int)(((int64_t)sh.np * slices + 255) / 256);
     e.pool = sh.g * e.pool_per;
     e.mblock = sh.nchunks * sh.hq;
-    e.norm_per = (std::min(sh.b, sh.n) + 3) / 4;
+    const int norm_rows = 256 / (sh.mq <= kNormShortBlocks ? 8 : 64);   // of a workgroup
+    e.norm_per = (std::min(sh.b, sh.n) + norm_rows - 1) / norm_rows;
     e.norm = sh.hq * e.norm_per;
     e.msum_per = (sh.mq + 63) / 64;
     e.msum = sh.hq * e.msum_per;

@@ -1,7 +1,8 @@
 """Estimation at the edges of its 64-key steps and their two 32-key tiles:
 lengths around the 32-row waves, where a step's second tile is left out (fp32)
-or masked, the last tokens' rows not aligned to the blocks, against a 64-bit
-reference.  One head, so the pooled heads are the strided inputs.
+or masked, the last tokens' rows not aligned to the blocks, 8 and 9 blocks (the
+rows' normalisers change their split there), against a 64-bit reference.  One
+head, so the pooled heads are the strided inputs.
 Tolerances: those of test_gpu_parity.py for block scores and masses."""
 import pytest
 
@@ -11,7 +12,7 @@ from tests.test_gpu_parity import LOGA_TOL, MASS_RTOL
 
 pytestmark = pytest.mark.gpu
 
-LENGTHS = [1, 16, 31, 32, 33, 63, 64, 65, 96, 97, 129, 161, 255, 300]
+LENGTHS = [1, 16, 31, 32, 33, 63, 64, 65, 96, 97, 129, 161, 255, 300, 512, 513, 1024, 1025]
 
 
 @pytest.mark.parametrize("d", [64, 128])
