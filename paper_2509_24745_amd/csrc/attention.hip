@@ -790,32 +790,44 @@ __global__ __launch_bounds__(2 * B * G, (AttnCfg<T, D, B>::min_waves(G))) void a
     // The first item of every workgroup is its own number's (the grid is a
     // multiple of kNumXcd); the counters hand out the rest, so a launch with
     // no more items than workgroups touches none.  Own XCD's queue first; once
-    // it is empty, the other queues in turn (their remaining items are their
-    // shortest), so no XCD idles while another still has work.  Every probe of
-    // an empty queue moves on, so the loop ends after at most kNumXcd of them.
-    // (One load of all counters instead of the probes kept up to a thousand
-    // workgroups waiting at the end: bf16, 32/8 heads, sparse, 1024 workgroups,
-    // K/V copy and attention, probes against the load: d 64 b 64 1.5K 19.6
-    // against 31.3 us, 2.1K 31.1 against 42.5, 4173 53.0 against 63.0, 20K 552
-    // against 558; with 256 or 512 workgroups the load was up to 3 us faster.
-    // A ticket for the first item as well: 1-2 us slower.)
-    int x = blockIdx.x % kNumXcd, pos = blockIdx.x / kNumXcd, empty = 0;
+    // it is empty, the others with items left in turn (their shortest), so no
+    // XCD idles while another still has work.  Whoever finds a queue empty sets
+    // its bit in one shared word and learns from it which others are empty
+    // too: the last workgroup ends after two round trips, with one request
+    // each.  A queue found empty stays empty, and a workgroup tries each once,
+    // so the loop ends after at most kNumXcd failures.  K/V copy and attention,
+    // sparse, 32/8 heads, against probing every queue / against a load of all
+    // counters (eight requests a workgroup, slow with 1024 of them), bf16: d 64
+    // b 64 4173 tokens 44.3 / 56.7 -> 42.1 us, d 128 b 64 62.7 / 72.5 -> 59.7, d 128
+    // b 128 63.4 / 62.8 -> 60.3; fp32 d 64 b 64 1.5K 47.6 / 45.8 -> 45.0, d 128 b 128
+    // 1.5K 96.8 / 92.2 -> 92.3.
+    int x = blockIdx.x % kNumXcd, pos = blockIdx.x / kNumXcd, item = x + kNumXcd * pos;
     for (;;) {
-        if (pos < per_queue) {
-            int m, i;
-            if (attn_item(sh, x + kNumXcd * pos, &m, &i))
-                attn_one<T, D, B, DENSE, G>(sh, q, kvb, block_count, block_index, out, lse, m, i, slot, grp, ml);
-            if (own == per_queue) break;
-        } else {
-            if (++empty == kNumXcd) break;
-            x = (x + 1) % kNumXcd;
+        int m, i;
+        if (attn_item(sh, item, &m, &i))
+            attn_one<T, D, B, DENSE, G>(sh, q, kvb, block_count, block_index, out, lse, m, i, slot, grp, ml);
+        if (own == per_queue) break;
+        if (threadIdx.x < 64) {   // wave 0
+            const int lane = threadIdx.x;
+            for (;;) {
+                if (lane == 0) pos = own + atomicAdd(queue + x * kQueueStride, 1);
+                pos = __builtin_amdgcn_readfirstlane(pos);
+                if (pos < per_queue) break;
+                int gone = 1 << x;
+                if (lane == 0) gone |= atomicOr(queue + kQueueGone, gone);
+                const unsigned left = ~__builtin_amdgcn_readfirstlane(gone) & ((1u << kNumXcd) - 1u);
+                if (!left) break;
+                const unsigned turn = left >> x | left << (kNumXcd - x);
+                x = (x + __builtin_ctz(turn)) % kNumXcd;
+            }
+            if (lane == 0) next_item = pos < per_queue ? x + kNumXcd * pos : -1;
         }
-        if (threadIdx.x == 0) next_item = own + atomicAdd(queue + x * kQueueStride, 1);
         // the barriers also keep the previous item's LDS reads ahead of the
         // next item's copies
         __syncthreads();
-        pos = __builtin_amdgcn_readfirstlane(next_item);
+        item = __builtin_amdgcn_readfirstlane(next_item);
         __syncthreads();
+        if (item < 0) break;
     }
 }
 

@@ -50,6 +50,8 @@ constexpr size_t kMallBytes = (size_t)256 << 20;
 // The attention kernel is persistent: its workgroups pull work items from
 // kNumXcd queues (one int32 counter per queue, each on its own 128-byte line).
 constexpr int kQueueStride = 32;
+// word of the queue region (in queue 0's line) with a bit for every queue found empty
+constexpr int kQueueGone = kQueueStride / 2;
 constexpr size_t kQueueBytes = (size_t)kNumXcd * kQueueStride * 4;
 
 // Size of the static device scratch array that the entry point which
